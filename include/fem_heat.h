@@ -84,7 +84,8 @@ extern "C" {
 #define FEM_DEVICE_PTRS 0x1u /* array arguments are device pointers               */
 #define FEM_TIMING 0x2u      /* time iteration kernels with HIP events (every 64th iteration and every
                                 8th residual replacement launched, counted across solves, so the
-                                events barely perturb the run) */
+                                events barely perturb the run); in the resident form (fem_heat_run)
+                                the same samples of its phases by the device's clock */
 #define FEM_ONE_REDUCTION 0x4u /* FP64 PCG in one kernel and one reduction per iteration: the direction
                                   kernel also completes the previous update (r -= alpha q, x += alpha d)
                                   and sums d^T q, q^T P^-1 r, q^T P^-1 q and r^T P^-1 r; alpha and the stop
@@ -227,9 +228,11 @@ typedef struct {
  * their summed durations, per kernel kind. */
 typedef struct {
   int64_t gather_launches;   /* search-direction + operator-apply kernel (q = A d, d^T q,
-                                and the previous iteration's x += alpha d)                  */
+                                and the previous iteration's x += alpha d); in the resident form
+                                the operator's march and the sum d^T q                       */
   double gather_ms;
-  int64_t update_launches;   /* r -= alpha q + preconditioned residual norm kernel        */
+  int64_t update_launches;   /* r -= alpha q + preconditioned residual norm kernel (in the resident
+                                form with the exchange of P^-1 r)                           */
   double update_ms;
   int64_t replace_launches;  /* residual-replacement gather kernel                        */
   double replace_ms;
@@ -261,7 +264,18 @@ int fem_heat_create(const fem_grid *grid, const double *k_e, const double *rhoc_
  * replacement and max_iter from the options.  Validates dt > 0,
  * theta in [0,1], rtol > 0, nsteps >= 0 (FEM_EINVAL).  Returns FEM_OK,
  * FEM_ENOCONV (some step hit max_iter: all outputs written, iters = max_iter
- * marks the step) or FEM_EBREAKDOWN (outputs up to the last good step). */
+ * marks the step) or FEM_EBREAKDOWN (outputs up to the last good step).
+ *
+ * A simulation whose grid fits on the chip (up to about 1.1 million nodes; the
+ * Jacobi preconditioner, no tile override, neither FEM_ONE_REDUCTION nor
+ * FEM_ONE_KERNEL) runs in the resident form: one kernel takes many steps, its
+ * blocks each keep a brick of the grid in LDS and registers and exchange sums
+ * and brick surfaces.  The same holds for batch members and served requests.
+ * The kernel needs all blocks of a simulation at once: resident launches of one
+ * process take turns where they would not all fit, and a launch whose blocks do
+ * not all get compute units within 20 ms (another process, or a stream with
+ * a compute-unit mask, holds them) does nothing, and the run goes on with the
+ * two-kernel form (whose fields agree to rounding). */
 int fem_heat_run(fem_heat *h, const double *T0, const double *T_prev, double dt, double theta,
                  int32_t nsteps, double rtol, fem_out *out);
 

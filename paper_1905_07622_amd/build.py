@@ -17,7 +17,11 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfemheat.so")
 INCLUDE = os.path.join(ROOT, "include")
 
-SOURCES = ["solver.hip", "engine.hip", "server.cpp", "capi.cpp", "tune_cache.cpp"]
+SOURCES = ["solver.hip", "engine.hip", "resident_f64.hip", "resident_mixed.hip", "resident_host.cpp", "server.cpp",
+           "capi.cpp", "tune_cache.cpp"]
+# The resident kernels keep their brick's vectors in register arrays indexed by
+# constants; promoted to vector registers first, the arrays spill.
+EXTRA_FLAGS = {src: ["-mllvm", "-disable-promote-alloca-to-vector"] for src in ("resident_f64.hip", "resident_mixed.hip")}
 ARCH = "gfx950"
 
 
@@ -37,7 +41,7 @@ def common_flags():
 
 def _compile(src: str, verbose: bool) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc()] + common_flags() + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [hipcc()] + common_flags() + EXTRA_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

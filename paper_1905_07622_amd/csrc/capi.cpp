@@ -266,10 +266,21 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
   // process gets by default).  Batches of small simulations are bound by
   // launches, not by their tails, and stay whole: 32 x 19k nodes ran 20%
   // slower as two.
-  uint64_t nodes = 0;
-  for (int32_t i = 0; i < n; ++i)
-    nodes += (uint64_t)(reqs[i].grid.nx + 1) * (uint64_t)(reqs[i].grid.ny + 1) * (uint64_t)(reqs[i].grid.nz + 1);
-  const int auto_g = (int)std::min<uint64_t>({3u, (uint64_t)n / 16u, nodes >> 21});
+  // Only members in the two-kernel form count: resident members iterate on
+  // their own compute units, not in lockstep, and fill the device in one launch.
+  uint64_t nodes = 0, lockstep = 0;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, o.device) != hipSuccess) {
+    g_create_error = "hipDeviceGetAttribute failed";
+    return FEM_EDEVICE;
+  }
+  for (int32_t i = 0; i < n; ++i) {
+    const fem_grid& g = reqs[i].grid;
+    if (femheat::resident_member(g, o, true, cus)) continue;
+    ++lockstep;
+    nodes += (uint64_t)(g.nx + 1) * (uint64_t)(g.ny + 1) * (uint64_t)(g.nz + 1);
+  }
+  const int auto_g = (int)std::min<uint64_t>({3u, lockstep / 16u, nodes >> 21});
   const int G = std::max(1, std::min<int>(n, o.batch_groups > 0 ? o.batch_groups : auto_g));
   hipStream_t caller = reinterpret_cast<hipStream_t>(o.hip_stream);
   std::vector<hipStream_t> gs((size_t)G, nullptr);

@@ -41,6 +41,7 @@
 #include "batch.hpp"
 #include "dirupd.hpp"
 #include "engine.hpp"
+#include "resident_host.hpp"
 #include "runtime.hpp"
 #include "tune.hpp"
 
@@ -80,6 +81,8 @@ struct Sim {
   int32_t it = 0, nsw = 0, xc = 0, exc = 0;
   bool sweeping = false, broke = false;
   Scalars so{}, si{};  // latest settled outer and inner state
+  bool resident = false;             // advances in resident launches
+  uint64_t res_count[2] = {0, 0};    // its iterations and replacements so far (timing samples)
 };
 
 namespace {
@@ -118,6 +121,7 @@ class Engine {
     dirupd_ = on && (opts_.flags & FEM_ONE_KERNEL) != 0;
     if (const char* v = std::getenv("FEMHEAT_BARRIER_SPIN_LIMIT")) bar_spin_ = (uint32_t)std::strtoul(v, nullptr, 10);
   }
+  void keep_stage(bool on) { keep_stage_ = on; }
   ~Engine() {
     (void)hipStreamSynchronize(stream_);
     efree(bar_count_);
@@ -130,6 +134,8 @@ class Engine {
     if (tab_host_) (void)hipHostFree(tab_host_);
     for (auto e : ev_) (void)hipEventDestroy(e);
     if (ev_decide_) (void)hipEventDestroy(ev_decide_);
+    efree(own_stage_.dev);
+    if (own_stage_.host) (void)hipHostFree(own_stage_.host);
     for (const Timed& t : pending_)
       for (hipEvent_t e : t.e)
         if (e) (void)hipEventDestroy(e);
@@ -156,7 +162,7 @@ class Engine {
     p = nullptr;
   }
   int run();
-  int step(int* active);
+  int step(int* active, int resident_steps);
   int write_outputs(Sim& s, float ms);
   void remove(Sim* s);
   std::vector<std::unique_ptr<Sim>>& sims() { return sims_; }
@@ -194,6 +200,11 @@ class Engine {
   template <typename V>
   int pcg(int first_chunk);
   int epoch();
+  int resident_pass(int max_steps, int* advanced);
+  int resident_result(Sim& s, const ResOut& out, const ResStep* rec);
+  int leave_resident(Sim& s);
+  ResStage own_stage_;       // buffers of resident launches
+  bool keep_stage_ = false;  // a run of one handle: they stay with the handle
   int mixed_sweeps();
   int finish_step(Sim& s);
   // Timing of sampled iterations: events come from a pool; a chunk's records
@@ -359,12 +370,8 @@ int Engine::add(const RunRequest& r, Sim** out) {
   RC_TRY(copy_in(h, s.T2, r.T_prev ? r.T_prev : r.T0, N));
   hipLaunchKernelGGL((apply_dirichlet_kernel<double>), dim3(nblk(N)), dim3(kT), 0, stream_, h->g, s.T1);
   hipLaunchKernelGGL((apply_dirichlet_kernel<double>), dim3(nblk(N)), dim3(kT), 0, stream_, h->g, s.T2);
-  // the first direction of every solve has beta = 0, but 0 * d must be 0
-  for (int k = 0; k < 2; ++k)
-    hipLaunchKernelGGL((fill_kernel<double>), dim3(nblk(N)), dim3(kT), 0, stream_, h->d64[k], 0.0, N);
-  if (mixed_)
-    for (int k = 0; k < 2; ++k)
-      hipLaunchKernelGGL((fill_kernel<float>), dim3(nblk(N)), dim3(kT), 0, stream_, h->d32[k], 0.0f, N);
+  s.resident = h->res.nblk > 0;
+  if (!s.resident) RC_TRY(leave_resident(s));
   HIP_TRY(hipGetLastError());
   const fem_out* o = r.out;
   s.first = o ? o->first_step : 0;
@@ -391,6 +398,24 @@ int Engine::add(const RunRequest& r, Sim** out) {
   if (out) *out = sp.get();
   sims_.push_back(std::move(sp));
   dirty_ = true;
+  return FEM_OK;
+}
+
+// Prepares a simulation for the two-kernel form (at the start of a run, or
+// after a resident launch that could not meet; the exchange vectors were the
+// directions and need values: the first beta of a solve is 0, but 0 * d must
+// be 0).
+int Engine::leave_resident(Sim& s) {
+  fem_heat* h = s.rq.h;
+  const uint32_t N = h->g.N;
+  s.resident = false;
+  dirty_ = true;
+  for (int k = 0; k < 2; ++k)
+    hipLaunchKernelGGL((fill_kernel<double>), dim3(nblk(N)), dim3(kT), 0, stream_, h->d64[k], 0.0, N);
+  if (mixed_)
+    for (int k = 0; k < 2; ++k)
+      hipLaunchKernelGGL((fill_kernel<float>), dim3(nblk(N)), dim3(kT), 0, stream_, h->d32[k], 0.0f, N);
+  HIP_TRY(hipGetLastError());
   return FEM_OK;
 }
 
@@ -494,7 +519,7 @@ int Engine::compose() {
   fem_heat* h = h_;
   std::vector<Sim*> next;
   for (auto& sp : sims_)
-    if (!sp->finished) next.push_back(sp.get());
+    if (!sp->finished && !sp->resident) next.push_back(sp.get());
   if (!dirty_ && next == act_ && full_.ngroups > 0) return FEM_OK;
   dirty_ = false;
   HIP_TRY(hipStreamSynchronize(stream_));  // buffers below may be freed or rewritten
@@ -1255,11 +1280,252 @@ int Engine::write_outputs(Sim& s, float ms) {
   return FEM_OK;
 }
 
-// One epoch: every simulation that still has steps advances by one step.
-// *active receives how many took part (0: nothing left to do).
-int Engine::step(int* active) {
+// ---- the resident form (resident.hpp) ----------------------------------------
+
+// Takes over what a launch did for one simulation.
+int Engine::resident_result(Sim& s, const ResOut& out, const ResStep* rec) {
+  fem_heat* h = s.rq.h;
+  for (int k = 0; k < out.steps; ++k) {
+    const ResStep& t = rec[k];
+    const int n = s.step;
+    s.iters[n] = t.iters;
+    s.sweeps[n] = t.sweeps;
+    s.relres[n] = t.delta_b > 0 ? std::sqrt(std::max(t.delta, 0.0) / t.delta_b) : 0.0;
+    const bool unconverged = mixed_ ? (t.delta > t.tol) : (t.iters >= opts_.max_iter && t.delta > t.tol);
+    if (unconverged && s.status == FEM_OK) s.status = FEM_ENOCONV;
+    s.total += t.iters;
+    s.est = std::max(1, t.iters);
+    double* freed = s.T2;  // the kernel's rotation
+    s.T2 = s.T1;
+    s.T1 = s.X[0];
+    s.X[0] = freed;
+    s.step = n + 1;
+  }
+  if (out.status != 0) {
+    if (s.status == FEM_OK || s.status == FEM_ENOCONV) s.status = FEM_EBREAKDOWN;
+    h->err = "PCG breakdown (d^T A d <= 0 or non-finite scalar)";
+    s.finished = true;
+  } else if (s.step >= s.rq.nsteps) {
+    s.finished = true;
+  }
+  const fem_out* o = s.rq.out;
+  if (out.steps > 0 && o && o->T_saved && o->save_every > 0 && s.step % o->save_every == 0)
+    RC_TRY(copy_out(h, o->T_saved + (size_t)(s.step / o->save_every - 1) * h->g.N, s.T1, (size_t)h->g.N * sizeof(double)));
+  if (timing_) {
+    int khz = 0;
+    HIP_TRY(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, h->opts.device));
+    const double ms = 1.0 / std::max(khz, 1);
+    stats.gather_launches += (int64_t)out.samples[0];
+    stats.gather_ms += (double)out.ticks[0] * ms;
+    stats.update_launches += (int64_t)out.samples[1];
+    stats.update_ms += (double)out.ticks[1] * ms;
+    stats.replace_launches += (int64_t)out.samples[2];
+    stats.replace_ms += (double)out.ticks[2] * ms;
+  }
+  s.res_count[0] = out.count[0];
+  s.res_count[1] = out.count[1];
+  return FEM_OK;
+}
+
+// Advances every resident simulation by up to max_steps steps (fewer at the
+// end of its run and at a step whose field is saved): one launch per element
+// kind and brick height.  *advanced receives how many took part.
+int Engine::resident_pass(int max_steps, int* advanced) {
+  fem_heat* h = h_;
+  *advanced = 0;
+  std::vector<Sim*> act;
+  for (auto& sp : sims_)
+    if (sp->resident && !sp->finished) act.push_back(sp.get());
+  if (act.empty()) return FEM_OK;
+  // launches: simulations of one element kind and brick height together
+  struct Launch {
+    int kind = 0, planes = 0, nthreads = 0;
+    uint32_t off = 0, blocks = 0;
+    size_t lds = 0;
+  };
+  std::vector<Launch> launches;
+  std::stable_sort(act.begin(), act.end(), [](const Sim* x, const Sim* y) {
+    const fem_heat *p = x->rq.h, *q = y->rq.h;
+    return p->kind != q->kind ? p->kind < q->kind : p->res.c < q->res.c;
+  });
+  const size_t n = act.size();
+  std::vector<int> steps(n);
+  std::vector<size_t> slot(n);
+  size_t nsteps = 0, nblocks = 0, nslots = 0;
+  uint32_t max_nodes = 0;
+  for (size_t k = 0; k < n; ++k) {
+    const Sim& s = *act[k];
+    const fem_heat* sh = s.rq.h;
+    int m = std::min(max_steps, s.rq.nsteps - s.step);
+    const fem_out* o = s.rq.out;
+    if (o && o->T_saved && o->save_every > 0) m = std::min(m, o->save_every - s.step % o->save_every);
+    steps[k] = m;
+    if (launches.empty() || launches.back().kind != sh->kind || launches.back().planes != sh->res.c) {
+      Launch l;
+      l.kind = sh->kind;
+      l.planes = sh->res.c;
+      l.off = (uint32_t)nblocks;
+      launches.push_back(l);
+    }
+    Launch& l = launches.back();
+    l.nthreads = std::max(l.nthreads, sh->res.nthreads);
+    l.lds = std::max(l.lds, res_lds(sh->res.a, sh->res.b, sh->res.c, 8));
+    l.blocks += sh->res.nblk;
+    nblocks += sh->res.nblk;
+    nsteps += (size_t)m;
+    slot[k] = nslots;
+    nslots += (size_t)2 * kResRep * sh->res.nblk * 2 + 2 + (size_t)sh->res.nblk * sh->res.nthreads * kResHalo;
+    max_nodes = std::max(max_nodes, sh->g.N);
+  }
+  // one buffer: records, block table, load factors and results (uploaded), step
+  // records (with the results, downloaded), slots and stash (on the device only)
+  auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+  const size_t o_tab = up(n * sizeof(ResSim)), o_fs = o_tab + up(nblocks * sizeof(uint2)),
+               o_out = o_fs + up(nsteps * sizeof(double)), o_rec = o_out + up(n * sizeof(ResOut)),
+               o_slot = o_rec + up(nsteps * sizeof(ResStep)), bytes = o_slot + up(nslots * 8);
+  // a single run keeps its buffers with the handle
+  ResStage& st = keep_stage_ ? act[0]->rq.h->res_stage : own_stage_;
+  if (st.cap < bytes || st.host_cap < o_slot) {
+    HIP_TRY(hipStreamSynchronize(stream_));
+    efree(st.dev);
+    if (st.host) (void)hipHostFree(st.host);
+    st = ResStage{};
+    RC_TRY(ealloc(&st.dev, bytes));
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&st.host), o_slot, hipHostMallocDefault));
+    st.cap = bytes;
+    st.host_cap = o_slot;
+  }
+  ResSim* sims = reinterpret_cast<ResSim*>(st.host);
+  uint2* tab = reinterpret_cast<uint2*>(st.host + o_tab);
+  double* fs = reinterpret_cast<double*>(st.host + o_fs);
+  ResOut* outs = reinterpret_cast<ResOut*>(st.host + o_out);
+  const ResStep* recs = reinterpret_cast<const ResStep*>(st.host + o_rec);
+  size_t at = 0, bt = 0;
+  std::vector<size_t> rec_at(n);
+  long meet_limit = -1;  // tests of a launch whose blocks do not meet
+  if (const char* v = std::getenv("FEMHEAT_RESIDENT_MEET_LIMIT")) meet_limit = std::strtol(v, nullptr, 10);
+  for (size_t k = 0; k < n; ++k) {
+    Sim& s = *act[k];
+    const fem_heat* sh = s.rq.h;
+    const double dt = s.rq.dt, theta = s.rq.theta;
+    ResSim& r = sims[k];
+    std::memset(static_cast<void*>(&r), 0, sizeof(r));
+    const GatherArgs<double> A = gather_args<double>(sh, 1.0, theta * dt), Lop = gather_args<double>(sh, 1.0, -(1.0 - theta) * dt);
+    r.g = sh->g;
+    r.s = sh->res;
+    r.rhoc64 = sh->rhoc64;
+    r.k64 = sh->k64;
+    r.sa64 = A.sa;
+    r.sbA64 = A.sb;
+    r.sbL64 = Lop.sb;
+    for (int c = 0; c < 8; ++c) {
+      r.Mc64[c] = A.Mc[c];
+      r.Kc64[c] = A.Kc[c];
+    }
+    // exchanged vectors: the handle's PCG vectors, which this form keeps on chip
+    if (mixed_) {
+      const GatherArgs<float> A32 = gather_args<float>(sh, 1.0, theta * dt);
+      r.rhoc32 = sh->rhoc32;
+      r.k32 = sh->k32;
+      r.sa32 = A32.sa;
+      r.sbA32 = A32.sb;
+      for (int c = 0; c < 8; ++c) {
+        r.Mc32[c] = A32.Mc[c];
+        r.Kc32[c] = A32.Kc[c];
+      }
+      r.pinv32 = sh->pinv32;
+      r.E[0] = sh->d32[0];
+      r.E[1] = sh->d32[1];
+      r.E[2] = sh->q32;
+      r.EX = sh->r32;
+      r.EX64 = sh->d64[0];
+    } else {
+      r.E[0] = sh->d64[0];
+      r.E[1] = sh->d64[1];
+      r.E[2] = sh->q64;
+      r.EX = sh->r64;
+    }
+    r.F = sh->F64;
+    r.pinv64 = sh->pinv64;
+    r.lift = sh->lift64;
+    r.b = sh->b64;
+    r.T[0] = s.T1;
+    r.T[1] = s.T2;
+    r.T[2] = s.X[0];
+    unsigned long long* words = reinterpret_cast<unsigned long long*>(st.dev + o_slot) + slot[k];
+    r.ctl = words;
+    r.slots = words + 2;
+    r.stash = r.slots + (size_t)2 * kResRep * sh->res.nblk * 2;
+    r.fs = reinterpret_cast<const double*>(st.dev + o_fs) + at;
+    r.rec = reinterpret_cast<ResStep*>(st.dev + o_rec) + at;
+    r.out = reinterpret_cast<ResOut*>(st.dev + o_out) + k;
+    r.xyz = sh->xyz_dev;
+    r.nsens = s.nsens;
+    r.traces = s.nsens > 0 ? sh->traces_dev + (size_t)s.step * s.nsens : nullptr;
+    r.rtol2 = s.rq.rtol * s.rq.rtol;
+    r.inner_rtol = opts_.inner_rtol;
+    r.spin_meet = meet_limit >= 0 ? (uint32_t)meet_limit : nblocks > (size_t)sh->cus ? kResMeetQueued : kResMeet;
+    r.spin = kResSpin;
+    r.nsteps = steps[k];
+    r.max_iter = opts_.max_iter;
+    r.stop_rule = opts_.stop_rule;
+    r.R = R_;
+    r.guess_prev = opts_.guess == FEM_GUESS_PREV ? 1 : 0;
+    r.max_refine = opts_.max_refine;
+    r.timing = timing_ ? 1 : 0;
+    ResOut& out = outs[k];
+    std::memset(static_cast<void*>(&out), 0, sizeof(out));
+    out.count[0] = s.res_count[0];
+    out.count[1] = s.res_count[1];
+    rec_at[k] = at;
+    for (int q = 0; q < steps[k]; ++q) fs[at++] = dt * schedule_value(sh, (int64_t)s.first + s.step + q + 1);
+    const uint32_t first = (uint32_t)k;
+    for (uint32_t b = 0; b < sh->res.nblk; ++b) tab[bt++] = make_uint2(first, b);
+  }
+  // The launch may have to wait for compute units while it holds some: what
+  // this stream was given before (by a caller, perhaps behind other work)
+  // comes to its end first.
+  HIP_TRY(hipStreamSynchronize(stream_));
+  const int cus = act[0]->rq.h->cus;
+  uint32_t want = 0;  // the most blocks at once, in whole rounds over the XCDs
+  for (const Launch& l : launches) want = std::max(want, (l.blocks + 7) / 8 * 8);
+  {
+    ResidentGate gate(act[0]->rq.h->opts.device, cus, (int)std::min<uint32_t>(want, (uint32_t)cus));
+    HIP_TRY(hipMemcpyAsync(st.dev, st.host, o_rec, hipMemcpyHostToDevice, stream_));
+    HIP_TRY(resident_reset(stream_, reinterpret_cast<const ResSim*>(st.dev), (uint32_t)n, mixed_, max_nodes));
+    for (const Launch& l : launches)
+      HIP_TRY(resident_launch(mixed_, l.kind, l.planes, l.blocks, l.nthreads, l.lds, stream_,
+                              reinterpret_cast<const ResSim*>(st.dev),
+                              n == 1 ? nullptr : reinterpret_cast<const uint2*>(st.dev + o_tab) + l.off));
+    HIP_TRY(hipMemcpyAsync(st.host + o_out, st.dev + o_out, o_slot - o_out, hipMemcpyDeviceToHost, stream_));
+    HIP_TRY(hipStreamSynchronize(stream_));
+  }
+  for (size_t k = 0; k < n; ++k) {
+    Sim& s = *act[k];
+    if (outs[k].state == RES_LOST)
+      return fail(h, FEM_EDEVICE, "a block of a resident launch stopped answering the others");
+    if (outs[k].state == RES_ABSENT) {  // other work held the device: nothing was done
+      RC_TRY(leave_resident(s));
+      continue;
+    }
+    RC_TRY(resident_result(s, outs[k], recs + rec_at[k]));
+  }
+  *advanced = (int)n;
+  return FEM_OK;
+}
+
+// One epoch: every simulation that still has steps advances by one step (in
+// the resident form by up to resident_steps).  *active receives how many took
+// part (0: nothing left to do).
+int Engine::step(int* active, int resident_steps) {
+  int advanced = 0;
+  RC_TRY(resident_pass(resident_steps, &advanced));
+  bool others = false;
+  for (auto& sp : sims_) others = others || (!sp->finished && !sp->resident);
+  *active = advanced;
+  if (!others) return FEM_OK;
   RC_TRY(compose());
-  *active = (int)act_.size();
+  *active += (int)act_.size();
   if (act_.empty()) return FEM_OK;
   return epoch();
 }
@@ -1270,7 +1536,7 @@ int Engine::run() {
   HIP_TRY(hipEventRecord(ev_run_[0], stream_));
   for (;;) {
     int active = 0;
-    RC_TRY(step(&active));
+    RC_TRY(step(&active, kResRunSteps));
     if (active == 0) break;
   }
   HIP_TRY(hipEventRecord(ev_run_[1], stream_));
@@ -1420,7 +1686,7 @@ int engine_tune(fem_heat* h, double dt, double theta, uint32_t flags, fem_tune_r
 Engine* engine_new(hipStream_t stream, const fem_opts& opts, fem_heat* err) { return new Engine(stream, opts, err); }
 void engine_delete(Engine* e) { delete e; }
 int engine_add(Engine* e, const RunRequest& r, Sim** out) { return e->add(r, out); }
-int engine_step(Engine* e, int* active) { return e->step(active); }
+int engine_step(Engine* e, int* active) { return e->step(active, kResServeSteps); }
 bool engine_sim_finished(const Sim* s) { return s->finished; }
 int engine_sim_status(const Sim* s) { return s->status; }
 int32_t engine_sim_steps(const Sim* s) { return s->step; }
@@ -1450,6 +1716,7 @@ int engine_run(const RunRequest* reqs, int32_t n, hipStream_t stream, const fem_
   // a run of one handle may iterate in one kernel; batches (and servers)
   // keep two, so a simulation's bits do not depend on what it runs with
   e.allow_one_kernel(one_kernel && n == 1);
+  e.keep_stage(one_kernel && n == 1);
   for (int32_t i = 0; i < n; ++i) {
     const int rc = e.add(reqs[i]);
     if (rc != FEM_OK) {

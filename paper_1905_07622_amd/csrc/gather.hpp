@@ -96,6 +96,94 @@ __device__ inline void read_plane(const V* P, int pw, int lx, int ly, PlaneQ<V>&
   q.b[3] = row0[2 * pw + 2];
 }
 
+// Contributions of one layer's 4 elements around a column to the two nodes
+// the layer joins: `lo_sum` on plane `lp` (other plane `hp`) and `hi_sum` on
+// `hp`; `down`: lp is the upper of the two.  coef(sx, sy, a, bk) gives an
+// element's scaled rho*c and k (s = 0: minus side, 1: plus side).  A node's
+// value is the sum of the contributions of its two layers, each computed here
+// from zero (explicit FMAs in a fixed order; the library is built without
+// automatic contraction) -- so it does not depend on the tiling or on the
+// direction of the march.  Each element's coefficients serve both nodes and
+// are then dead.
+template <typename V, int KIND, class Coef>
+__device__ __forceinline__ void layer_contributions(const PlaneQ<V>& lp, const PlaneQ<V>& hp, bool down, Coef coef,
+                                                    const V* Mc, const V* Kc, V& lo_sum, V& hi_sum) {
+  V plo[4], phi[4];
+  // the tetrahedra are not symmetric under z-reflection: their corners
+  // are taken on the physical bottom and top planes of the layer (which
+  // are hp and lp when the chunk marches down)
+  PlaneQ<V> bot, top;
+  if constexpr (KIND == kElemTet6) {
+    bot = down ? hp : lp;
+    top = down ? lp : hp;
+  }
+#pragma unroll
+  for (int sy = 0; sy < 2; ++sy) {
+#pragma unroll
+    for (int sx = 0; sx < 2; ++sx) {
+      const int e = sy * 2 + sx;
+      V a, bk;
+      coef(sx, sy, a, bk);
+      const V xl = sx ? lp.xp : lp.xm, yl = sy ? lp.yp : lp.ym, bl = lp.b[e];
+      const V xh = sx ? hp.xp : hp.xm, yh = sy ? hp.yp : hp.ym, bh = hp.b[e];
+      if constexpr (KIND == kElemTet6) {
+        // rows of the bottom node (corner ax + 2ay) and the top node (+4)
+        // of this element against its 8 corner values, zero entries skipped
+        const int ax = 1 - sx, ay = 1 - sy;
+        V val[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+          const PlaneQ<V>& P = (b >> 2) ? top : bot;
+          const bool dx = (b & 1) != ax, dy = ((b >> 1) & 1) != ay;
+          val[b] = dx ? (dy ? P.b[e] : (sx ? P.xp : P.xm)) : (dy ? (sy ? P.yp : P.ym) : P.c);
+        }
+        V rows[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          const int arow = ax + 2 * ay + 4 * r;
+          V acc = V(0);
+#pragma unroll
+          for (int b = 0; b < 8; ++b) {
+            const int m = kTetM[arow][b], kk = kTetK[arow][b];
+            if (m == 0 && kk == 0) continue;
+            const V c = m == 0 ? bk * V(kk) : (kk == 0 ? a * V(m) : fma(a, V(m), bk * V(kk)));
+            acc = fma(c, val[b], acc);
+          }
+          rows[r] = acc;
+        }
+        plo[e] = down ? rows[1] : rows[0];
+        phi[e] = down ? rows[0] : rows[1];
+      } else if constexpr (KIND == kElemCubic) {
+        // classes by popcount: c0 = 8a+4b, c1 = 4a, c2 = 2a-b, c3 = a-b
+        const V c0 = fma(V(8), a, V(4) * bk), c1 = V(4) * a, c2 = fma(V(2), a, -bk), c3 = a - bk;
+        V u = c0 * lp.c;
+        u = fma(c1, (xl + yl) + hp.c, u);
+        u = fma(c2, bl + (xh + yh), u);
+        plo[e] = fma(c3, bh, u);
+        V w = c0 * hp.c;
+        w = fma(c1, (xh + yh) + lp.c, w);
+        w = fma(c2, bh + (xl + yl), w);
+        phi[e] = fma(c3, bl, w);
+      } else {
+        const V vl[8] = {lp.c, xl, yl, bl, hp.c, xh, yh, bh};  // corner differing by class c
+        const V vh[8] = {hp.c, xh, yh, bh, lp.c, xl, yl, bl};
+        V c = fma(a, Mc[0], bk * Kc[0]);
+        V u = c * vl[0], w = c * vh[0];
+#pragma unroll
+        for (int k = 1; k < 8; ++k) {
+          c = fma(a, Mc[k], bk * Kc[k]);
+          u = fma(c, vl[k], u);
+          w = fma(c, vh[k], w);
+        }
+        plo[e] = u;
+        phi[e] = w;
+      }
+    }
+  }
+  lo_sum = (plo[0] + plo[1]) + (plo[2] + plo[3]);
+  hi_sum = (phi[0] + phi[1]) + (phi[2] + phi[3]);
+}
+
 // Staging slots: thread t stages LDS entries t and t + nthreads of a plane
 // tile (and of a coefficient tile); the launch guarantees both tiles fit.
 constexpr int kSlots = 2;
@@ -341,90 +429,13 @@ __device__ inline void gather_tile(const GatherArgs<V>& ga, Pro pro, Epi epi, co
     PlaneQ<V> lo, hi;
     V carry = V(0);
     V rn_lo = V(0), pp_lo = V(0), rn_hi = V(0), pp_hi = V(0);  // one-reduction form: own node's r, P^-1
-    // Contributions of one layer's 4 elements to the two nodes of this
-    // column that the layer joins: `lo` on plane `lp` (other plane `hp`) and
-    // `hi` on `hp`.  A node's value is the sum of the contributions of its two
-    // layers, each computed here from zero (explicit FMAs in a fixed order;
-    // the library is built without automatic contraction) -- so it does not
-    // depend on the tiling or on the direction of the march.  Each element's
-    // coefficients serve both nodes and are then dead.
     auto contributions = [&](const PlaneQ<V>& lp, const PlaneQ<V>& hp, const V* C, V& lo_sum, V& hi_sum) {
-      V plo[4], phi[4];
-      // the tetrahedra are not symmetric under z-reflection: their corners
-      // are taken on the physical bottom and top planes of the layer (which
-      // are hp and lp when the chunk marches down)
-      PlaneQ<V> bot, top;
-      if constexpr (KIND == kElemTet6) {
-        bot = down ? hp : lp;
-        top = down ? lp : hp;
-      }
-#pragma unroll
-      for (int sy = 0; sy < 2; ++sy) {
-#pragma unroll
-        for (int sx = 0; sx < 2; ++sx) {
-          const int e = sy * 2 + sx;
-          const int ci = (lty + sy) * CW + ltx + sx;
-          const V xl = sx ? lp.xp : lp.xm, yl = sy ? lp.yp : lp.ym, bl = lp.b[e];
-          const V xh = sx ? hp.xp : hp.xm, yh = sy ? hp.yp : hp.ym, bh = hp.b[e];
-          if constexpr (KIND == kElemTet6) {
-            // rows of the bottom node (corner ax + 2ay) and the top node (+4)
-            // of this element against its 8 corner values, zero entries skipped
-            const V a = C[ci], bk = C[CS + ci];
-            const int ax = 1 - sx, ay = 1 - sy;
-            V val[8];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-              const PlaneQ<V>& P = (b >> 2) ? top : bot;
-              const bool dx = (b & 1) != ax, dy = ((b >> 1) & 1) != ay;
-              val[b] = dx ? (dy ? P.b[e] : (sx ? P.xp : P.xm)) : (dy ? (sy ? P.yp : P.ym) : P.c);
-            }
-            V rows[2];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-              const int arow = ax + 2 * ay + 4 * r;
-              V acc = V(0);
-#pragma unroll
-              for (int b = 0; b < 8; ++b) {
-                const int m = kTetM[arow][b], kk = kTetK[arow][b];
-                if (m == 0 && kk == 0) continue;
-                const V c = m == 0 ? bk * V(kk) : (kk == 0 ? a * V(m) : fma(a, V(m), bk * V(kk)));
-                acc = fma(c, val[b], acc);
-              }
-              rows[r] = acc;
-            }
-            plo[e] = down ? rows[1] : rows[0];
-            phi[e] = down ? rows[0] : rows[1];
-          } else if constexpr (KIND == kElemCubic) {
-            // classes by popcount: c0 = 8a+4b, c1 = 4a, c2 = 2a-b, c3 = a-b
-            const V a = C[ci], bk = C[CS + ci];
-            const V c0 = fma(V(8), a, V(4) * bk), c1 = V(4) * a, c2 = fma(V(2), a, -bk), c3 = a - bk;
-            V u = c0 * lp.c;
-            u = fma(c1, (xl + yl) + hp.c, u);
-            u = fma(c2, bl + (xh + yh), u);
-            plo[e] = fma(c3, bh, u);
-            V w = c0 * hp.c;
-            w = fma(c1, (xh + yh) + lp.c, w);
-            w = fma(c2, bh + (xl + yl), w);
-            phi[e] = fma(c3, bl, w);
-          } else {
-            const V a = C[ci], bk = C[CS + ci];
-            const V vl[8] = {lp.c, xl, yl, bl, hp.c, xh, yh, bh};  // corner differing by class c
-            const V vh[8] = {hp.c, xh, yh, bh, lp.c, xl, yl, bl};
-            V c = fma(a, ga.Mc[0], bk * ga.Kc[0]);
-            V u = c * vl[0], w = c * vh[0];
-#pragma unroll
-            for (int k = 1; k < 8; ++k) {
-              c = fma(a, ga.Mc[k], bk * ga.Kc[k]);
-              u = fma(c, vl[k], u);
-              w = fma(c, vh[k], w);
-            }
-            plo[e] = u;
-            phi[e] = w;
-          }
-        }
-      }
-      lo_sum = (plo[0] + plo[1]) + (plo[2] + plo[3]);
-      hi_sum = (phi[0] + phi[1]) + (phi[2] + phi[3]);
+      auto coef = [&](int sx, int sy, V& a, V& bk) {
+        const int ci = (lty + sy) * CW + ltx + sx;
+        a = C[ci];
+        bk = C[CS + ci];
+      };
+      layer_contributions<V, KIND>(lp, hp, down, coef, ga.Mc, ga.Kc, lo_sum, hi_sum);
     };
     // Layer k: completes node vis(k) (its other layer was layer k-1) and
     // starts node vis(k+1).  Loads for plane vis(k+3) and layer k+2 are issued

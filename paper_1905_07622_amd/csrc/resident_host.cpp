@@ -1,0 +1,119 @@
+// Host side of the resident form: see resident_host.hpp.
+#include "resident_host.hpp"
+
+#include <algorithm>
+#include <array>
+#include <condition_variable>
+#include <mutex>
+
+
+namespace femheat {
+
+const void* resident_kernel_f64(int kind, int planes);    // resident_f64.hip
+const void* resident_kernel_mixed(int kind, int planes);  // resident_mixed.hip
+
+namespace {
+
+// Planes of a brick the kernels are built for: odd, so that the columns of a
+// wave lie in distinct LDS banks (see kResPitch).
+constexpr int kResPlanes[] = {3, 5, 9};
+
+constexpr int kMaxDevices = 64;
+
+struct GateState {
+  std::mutex mu;
+  std::condition_variable cv;
+  int taken = 0, total = 0;
+  uint64_t next = 0, serving = 0;
+};
+std::array<GateState, kMaxDevices>& gates() {
+  static std::array<GateState, kMaxDevices> g;
+  return g;
+}
+
+}  // namespace
+
+// Estimated microseconds of an iteration of a cut, from measurements of its
+// parts (MI355X): the two sums and the exchange take 4.0 us for 8 blocks and
+// 6.9 us for 252; a layer of the march 0.22 us for one wave per SIMD and
+// 0.4 us for two; a halo entry per thread 0.08 us.  A simulation alone takes
+// the cut with the shortest iteration; a batch member the one with the least
+// iteration time per compute unit, as other members fill the rest.
+ResShape resident_shape(const Geom& g, const fem_opts& o, bool batched, int cus) {
+  ResShape best{};
+  double best_t = 0.0;
+  // the form is Algorithm 1 with the Jacobi preconditioner and two sums per
+  // iteration; a caller that names a gather tile, or another form of the
+  // iteration, gets the kernels it names
+  if (o.precond != FEM_PRECOND_JACOBI || (o.flags & (FEM_ONE_REDUCTION | FEM_ONE_KERNEL)) || o.tile_x != 0 ||
+      o.tile_y != 0 || o.tile_z != 0)
+    return best;
+  const int limit = std::min(cus, kResBlocks);
+  for (int nbx = 1; nbx <= g.px; ++nbx) {
+    const int a = (g.px + nbx - 1) / nbx;
+    if ((g.px + a - 1) / a != nbx || a > kResThreads) continue;
+    if (nbx > limit) break;
+    for (int nby = 1; nby <= g.py; ++nby) {
+      const int b = (g.py + nby - 1) / nby;
+      if (nbx * nby > limit) break;
+      if ((g.py + b - 1) / b != nby || a * b > kResThreads) continue;
+      const int nt = (a * b + 63) / 64 * 64;
+      for (int c : kResPlanes) {
+        const int nbz = (g.pz + c - 1) / c;
+        const int64_t nblk = (int64_t)nbx * nby * nbz;
+        if (nblk > limit || res_lds(a, b, c, 8) > kResLds) continue;
+        const int halo = 2 * (a + 2) * (b + 2) + c * (2 * (a + 2) + 2 * b);
+        const int per = (halo + nt - 1) / nt;
+        if (per > kResHalo) continue;
+        const double march = (c + 1) * std::max(0.22, 0.2 * ((nt + 255) / 256));
+        const double iter = (nblk > 1 ? 4.0 + 0.0115 * (double)nblk : 1.0) + march + 0.08 * per;
+        const double t = batched ? iter * (double)nblk : iter;
+        if (best.nblk == 0 || t < best_t) {
+          best = ResShape{a, b, c, nbx, nby, nbz, (uint32_t)nblk, nt};
+          best_t = t;
+        }
+      }
+    }
+  }
+  return best;
+}
+
+bool resident_member(const fem_grid& grid, const fem_opts& o, bool batched, int cus) {
+  Geom g{};
+  g.px = grid.nx + 1;
+  g.py = grid.ny + 1;
+  g.pz = grid.nz + 1;
+  return resident_shape(g, o, batched, cus).nblk > 0;
+}
+
+hipError_t resident_launch(bool mixed, int kind, int planes, uint32_t blocks, int nthreads, size_t lds,
+                           hipStream_t stream, const ResSim* sims, const uint2* table) {
+  const void* fn = mixed ? resident_kernel_mixed(kind, planes) : resident_kernel_f64(kind, planes);
+  if (!fn) return hipErrorInvalidValue;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  void* args[] = {&sims, &table};
+  return hipLaunchKernel(fn, dim3(blocks), dim3((uint32_t)nthreads), args, lds, stream);
+}
+
+ResidentGate::ResidentGate(int device, int cus, int want) : device_(device), want_(std::min(want, cus)) {
+  GateState& s = gates()[(size_t)device];
+  std::unique_lock<std::mutex> lk(s.mu);
+  s.total = cus;
+  const uint64_t me = s.next++;
+  s.cv.wait(lk, [&] { return s.serving == me && s.taken + want_ <= s.total; });
+  s.taken += want_;
+  ++s.serving;
+  s.cv.notify_all();
+}
+
+ResidentGate::~ResidentGate() {
+  GateState& s = gates()[(size_t)device_];
+  {
+    std::lock_guard<std::mutex> lk(s.mu);
+    s.taken -= want_;
+  }
+  s.cv.notify_all();
+}
+
+}  // namespace femheat

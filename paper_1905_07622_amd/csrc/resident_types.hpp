@@ -1,0 +1,79 @@
+// Records and limits of the resident form (resident.hpp) that its host side
+// shares with the kernels.
+#pragma once
+
+#include "common.hpp"
+#include "solver.hpp"
+
+namespace femheat {
+
+constexpr int kResThreads = 512;   // most threads of a block (two waves per SIMD: 256 registers each)
+constexpr int kResBlocks = 256;    // most blocks of a simulation (one per CU)
+constexpr int kResHalo = 5;        // most halo nodes per thread
+constexpr int kResRep = 8;         // copies of each partial
+constexpr size_t kResLds = 160 * 1024 - 1024;  // dynamic LDS of a block (the rest: sums and flags)
+
+// Polls before a wait gives up (about 0.7 us each).  The meeting: 20 ms; in a
+// launch with more blocks than compute units, where the blocks of a later
+// simulation wait for an earlier one's to end, 20 s.  Any other wait: 2 s.
+constexpr uint32_t kResMeet = 30000, kResMeetQueued = 30000000, kResSpin = 3000000;
+
+// Steps per launch of a run, and of a server's epoch (which takes
+// cancellations and admissions in between).
+constexpr int kResRunSteps = 128, kResServeSteps = 4;
+
+// What a step reports.
+struct ResStep {
+  int32_t iters, sweeps;
+  double delta, delta_b, tol;
+};
+
+enum ResState : int32_t { RES_ABSENT = 0, RES_RAN = 1, RES_LOST = 3 };
+
+// What a launch reports per simulation.
+struct ResOut {
+  int32_t state;   // RES_ABSENT: not every block was resident in time, nothing was done
+  int32_t steps;   // steps completed
+  int32_t status;  // 0 or kStatusBreakdown (in the step after the completed ones)
+  int32_t pad;
+  uint64_t samples[3];  // timed direction gathers, updates and replacements
+  uint64_t ticks[3];    // and their summed durations (device clock ticks)
+  uint64_t count[2];    // iterations and replacements so far (for the next launch)
+};
+
+// One simulation of a launch.
+struct ResSim {
+  Geom g;
+  ResShape s;
+  const double *rhoc64, *k64;
+  const float *rhoc32, *k32;
+  double sa64, sbA64, sbL64, Mc64[8], Kc64[8];
+  float sa32, sbA32, Mc32[8], Kc32[8];
+  const double *F, *pinv64, *lift;
+  const float* pinv32;
+  double* b;
+  double* T[3];    // T^{n-1}, T^{n-2} and a third buffer, rotated from step to step
+  void* E[3];      // exchanged P^-1 r (the iterations' precision), used in turn
+  void* EX;        // exchanged iterate of a replacement (the iterations' precision)
+  double* EX64;    // mixed form: exchanged FP64 iterate of a correction
+  void* stash;     // the direction's halo during a replacement: kResHalo values per thread
+  unsigned long long* slots;  // 2 sets x kResRep x nblk partials of two words
+  unsigned long long* ctl;    // [0] rendezvous, [1] lost
+  const double* fs;           // dt * s_n of the launch's steps
+  ResStep* rec;               // of the launch's steps
+  const double* xyz;
+  double* traces;             // of the launch's steps
+  ResOut* out;
+  double rtol2, inner_rtol;
+  uint32_t spin_meet, spin;   // polls before a wait gives up
+  int32_t nsens, nsteps, max_iter, stop_rule, R, guess_prev, max_refine, timing;
+};
+
+// Values of a brick's node array: its columns with the halo, and one column
+// that takes the writes of lanes without a node; a multiple of 4 (alignment).
+__host__ __device__ constexpr int res_nodes(int a, int b, int c) { return (((a + 2) * (b + 2) + 1) * (c + 2) + 3) / 4 * 4; }
+__host__ __device__ constexpr size_t res_lds(int a, int b, int c, size_t w) {
+  return w * ((size_t)res_nodes(a, b, c) + 2 * (size_t)(a + 1) * (b + 1) * (c + 2));
+}
+
+}  // namespace femheat

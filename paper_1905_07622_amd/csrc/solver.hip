@@ -14,6 +14,7 @@
 
 #include "ebe.hpp"
 #include "engine.hpp"
+#include "resident_host.hpp"
 #include "rowwave.hpp"
 #include "runtime.hpp"
 #include "tune.hpp"
@@ -473,6 +474,8 @@ int solver_init(fem_heat* h, const fem_grid* grid, const double* k_e, const doub
     if (!h->batched && so.tile_x == 0 && h->shape.nthreads > kMaxBatchThreads && 10 * h->shape.ntiles < 9u * cus)
       h->shape = rule(false, &cap);
     h->capacity = cap;
+    h->cus = cus;
+    h->res = resident_shape(g, h->opts, h->batched, cus);
   }
   {
     const GatherShape& s = h->shape;
@@ -798,6 +801,9 @@ void solver_free(fem_heat* h) {
   dfree(h, h->xyz_dev);
   dfree(h, h->traces_dev);
   dfree(h, h->ebe_part);
+  dfree(h, h->res_stage.dev);
+  if (h->res_stage.host) (void)hipHostFree(h->res_stage.host);
+  h->res_stage = ResStage{};
   for (auto& e : h->ev_apply)
     if (e) (void)hipEventDestroy(e);
   if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);

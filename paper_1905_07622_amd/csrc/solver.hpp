@@ -16,6 +16,21 @@ struct RelayCtx {
   Scalars* S[2] = {nullptr, nullptr};
   double* P[2] = {nullptr, nullptr};
 };
+
+// Cut of a simulation into bricks for the resident form (resident.hpp).
+struct ResShape {
+  int32_t a, b, c;        // nodes of a brick
+  int32_t nbx, nby, nbz;  // bricks per axis
+  uint32_t nblk;          // bricks (= blocks); 0: the simulation does not run in this form
+  int32_t nthreads;
+};
+
+// Buffers of a resident launch: the records and results, pinned and on the device.
+struct ResStage {
+  unsigned char* host = nullptr;
+  unsigned char* dev = nullptr;
+  size_t cap = 0, host_cap = 0;
+};
 }  // namespace femheat
 
 struct fem_heat {
@@ -87,6 +102,11 @@ struct fem_heat {
   bool tuned = false;     // the shape came from the autotuner's cache
   uint32_t upd_blocks64 = 0, upd_blocks32 = 0, start_blocks = 0;
 
+  // resident form: the cut (nblk = 0: two kernels) and a single run's buffers
+  femheat::ResShape res{};
+  femheat::ResStage res_stage;
+  int32_t cus = 1;
+
   // element-by-element apply (test hook): 4 N partial sums, allocated on first use
   double* ebe_part = nullptr;
   hipEvent_t ev_apply[2] = {nullptr, nullptr};  // FEM_TIMING: around an apply's operator kernels
@@ -109,6 +129,9 @@ int solver_apply(fem_heat* h, int32_t which, double dt, double theta, const doub
 int solver_apply_noalloc(fem_heat* h, int32_t which, double dt, double theta, const double* x, double* y);
 int noalloc_scratch_setup(fem_heat* h);
 void solver_free(fem_heat* h);
+
+// Whether a simulation runs in the resident form (resident_host.cpp).
+bool resident_member(const fem_grid& g, const fem_opts& o, bool batched, int cus);
 
 // Time stepping (engine.hip): one handle, or a batch of handles advanced
 // together (status[i] receives the outcome of sims[i]).

@@ -301,18 +301,16 @@ __global__ void scale_kernel(const V* __restrict__ a, const V* __restrict__ x, d
   if (i < n) y[i] = (double)(a[i] * (V)x[i]);
 }
 
-// Field value at points: trilinear interpolation in the containing element
-// (lowest-index element on shared faces).  Traces row-major [step][sensor].
-[[maybe_unused]] static __global__ void sensor_kernel(Geom g, const double* __restrict__ T, const double* __restrict__ xyz, int32_t S,
-                              double* __restrict__ out) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= S) return;
+// Field value at point q of xyz: trilinear interpolation in the containing
+// element (lowest-index element on shared faces); T(i) reads node i.
+template <class Load>
+__device__ inline double sensor_value(const Geom& g, const double* __restrict__ xyz, int q, Load T) {
   const int n[3] = {g.nx, g.ny, g.nz};
   const double h[3] = {g.hx, g.hy, g.hz};
   int e[3];
   double xi[3];
   for (int d = 0; d < 3; ++d) {
-    const double t = xyz[3 * s + d] / h[d];
+    const double t = xyz[3 * q + d] / h[d];
     int k = (int)ceil(t) - 1;
     k = k < 0 ? 0 : (k > n[d] - 1 ? n[d] - 1 : k);
     double loc = t - (double)k;
@@ -338,18 +336,25 @@ __global__ void scale_kernel(const V* __restrict__ a, const V* __restrict__ x, d
       if (k > 0) a |= 1 << o[k - 1];
       const uint32_t i = (uint32_t)(e[0] + (a & 1)) +
                          (uint32_t)g.px * ((uint32_t)(e[1] + ((a >> 1) & 1)) + (uint32_t)g.py * (uint32_t)(e[2] + (a >> 2)));
-      v += lam[k] * T[i];
+      v += lam[k] * T(i);
     }
-    out[s] = v;
-    return;
+    return v;
   }
   for (int a = 0; a < 8; ++a) {
     const int ax = a & 1, ay = (a >> 1) & 1, az = (a >> 2) & 1;
     const double w = (ax ? xi[0] : 1.0 - xi[0]) * (ay ? xi[1] : 1.0 - xi[1]) * (az ? xi[2] : 1.0 - xi[2]);
     const uint32_t i = (uint32_t)(e[0] + ax) + (uint32_t)g.px * ((uint32_t)(e[1] + ay) + (uint32_t)g.py * (uint32_t)(e[2] + az));
-    v += w * T[i];
+    v += w * T(i);
   }
-  out[s] = v;
+  return v;
+}
+
+// Traces row-major [step][sensor].
+[[maybe_unused]] static __global__ void sensor_kernel(Geom g, const double* __restrict__ T, const double* __restrict__ xyz, int32_t S,
+                              double* __restrict__ out) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= S) return;
+  out[s] = sensor_value(g, xyz, s, [&](uint32_t i) { return T[i]; });
 }
 
 }  // namespace femheat
