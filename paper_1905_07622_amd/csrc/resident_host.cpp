@@ -33,12 +33,17 @@ std::array<GateState, kMaxDevices>& gates() {
 
 }  // namespace
 
-// Estimated microseconds of an iteration of a cut, from measurements of its
-// parts (MI355X): the two sums and the exchange take 4.0 us for 8 blocks and
-// 6.9 us for 252; a layer of the march 0.22 us for one wave per SIMD and
-// 0.4 us for two; a halo entry per thread 0.08 us.  A simulation alone takes
-// the cut with the shortest iteration; a batch member the one with the least
-// iteration time per compute unit, as other members fill the rest.
+// Estimated microseconds of an iteration of a cut, a linear fit to 250 cuts
+// measured on grids of 17^3, 49^3, 58 x 84 x 40 (stretched), 91 x 91 x 31
+// (tetrahedra) and 101^3 nodes (MI355X, FP64): the two sums take 3.8 us and
+// 6.7 ns per block, a layer of the march 0.38 us with one wave per SIMD and
+// 0.55 us with two, a halo node that a brick shares across an x-face 4.5 ns
+// (its values lie a row apart) and any other 0.7 ns.  So full rows and low
+// bricks win where they fit: 49^3 as 49 x 5 x 3 takes 6.9 us, as 25 x 10 x 5
+// 7.8 us, as 49 x 10 x 9 10.3 us; 17^3 as 17 x 6 x 3 6.7 us, in two bricks
+// 11.6 us.  A simulation alone takes the cut with the shortest iteration; a
+// batch member the one with the least iteration time per compute unit, as
+// other members fill the rest.
 ResShape resident_shape(const Geom& g, const fem_opts& o, bool batched, int cus) {
   ResShape best{};
   double best_t = 0.0;
@@ -65,8 +70,9 @@ ResShape resident_shape(const Geom& g, const fem_opts& o, bool batched, int cus)
         const int halo = 2 * (a + 2) * (b + 2) + c * (2 * (a + 2) + 2 * b);
         const int per = (halo + nt - 1) / nt;
         if (per > kResHalo) continue;
-        const double march = (c + 1) * std::max(0.22, 0.2 * ((nt + 255) / 256));
-        const double iter = (nblk > 1 ? 4.0 + 0.0115 * (double)nblk : 1.0) + march + 0.08 * per;
+        const int xface = nbx > 1 ? 2 * b * c : 0, rest = 2 * (a + 2) * (b + 2) + 2 * (a + 2) * c;
+        const double iter = (nblk > 1 ? 3.8 + 0.0067 * (double)nblk + 0.0045 * xface + 0.0007 * rest : 1.0) +
+                            (c + 1) * (nt <= 256 ? 0.38 : 0.55);
         const double t = batched ? iter * (double)nblk : iter;
         if (best.nblk == 0 || t < best_t) {
           best = ResShape{a, b, c, nbx, nby, nbz, (uint32_t)nblk, nt};
