@@ -11,11 +11,15 @@
 #include <thread>
 #include <vector>
 
+#include "checks.hpp"
 #include "engine.hpp"
 #include "server.hpp"
 #include "solver.hpp"
 
 namespace {
+
+using femheat::check_coefficients_on_device;
+using femheat::CoefficientArrays;
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
@@ -71,9 +75,11 @@ int check_opts(const fem_opts* opts, fem_opts& o, std::string& why) {
   return FEM_OK;
 }
 
-// Grid, coefficients and boundary conditions of a problem.
+// Grid, coefficients and boundary conditions of a problem.  checked: the
+// coefficients' flags of check_coefficients_on_device, or nullptr (they are
+// read here).
 int check_problem(const fem_grid* grid, const double* k_e, const double* rhoc_e, const fem_bc* bc, const fem_opts& o,
-                  std::string& why) {
+                  std::string& why, const int32_t* checked = nullptr) {
   auto bad = [&](const char* m) {
     why = m;
     return FEM_EINVAL;
@@ -100,6 +106,14 @@ int check_problem(const fem_grid* grid, const double* k_e, const double* rhoc_e,
   if (dev && hipSetDevice(o.device) != hipSuccess) {
     why = "hipSetDevice failed";
     return FEM_EDEVICE;
+  }
+  int32_t flags = 0;
+  const CoefficientArrays arrays{k_e, rhoc_e, E};
+  if (dev && !checked && check_coefficients_on_device(&arrays, 1, o.device, &flags)) checked = &flags;
+  if (checked) {
+    if (*checked & 1) return bad("k_e must be finite and >= 0");
+    if (*checked & 2) return bad("rhoc_e must be finite and > 0");
+    return FEM_OK;
   }
   std::vector<double> chk;
   if (!fetch(k_e, E, dev, chk)) {
@@ -224,12 +238,26 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
   fem_opts o;
   int rc = check_opts(opts, o, g_create_error);
   if (rc != FEM_OK) return rc;
-  // validate every request before anything runs
+  // validate every request before anything runs; coefficients in device memory
+  // are looked through there, all requests' at once
+  std::vector<int32_t> flags;
+  if (o.flags & FEM_DEVICE_PTRS) {
+    std::vector<CoefficientArrays> arrays;
+    bool plain = hipSetDevice(o.device) == hipSuccess;
+    for (int32_t i = 0; i < n && plain; ++i) {
+      const fem_grid& g = reqs[i].grid;
+      plain = g.nx >= 1 && g.ny >= 1 && g.nz >= 1 && reqs[i].k_e && reqs[i].rhoc_e &&
+              (double)(g.nx + 1) * (g.ny + 1) * (g.nz + 1) < 536870912.0;
+      if (plain) arrays.push_back({reqs[i].k_e, reqs[i].rhoc_e, (size_t)g.nx * g.ny * g.nz});
+    }
+    flags.assign((size_t)n, 0);
+    if (!plain || !check_coefficients_on_device(arrays.data(), n, o.device, flags.data())) flags.clear();
+  }
   int first_bad = FEM_OK;
   for (int32_t i = 0; i < n && first_bad == FEM_OK; ++i) {
     const fem_request& r = reqs[i];
     std::string why;
-    int v = check_problem(&r.grid, r.k_e, r.rhoc_e, &r.bc, o, why);
+    int v = check_problem(&r.grid, r.k_e, r.rhoc_e, &r.bc, o, why, flags.empty() ? nullptr : &flags[(size_t)i]);
     if (v == FEM_OK) {
       femheat::Geom g{};
       g.nx = r.grid.nx;
