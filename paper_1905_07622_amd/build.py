@@ -17,11 +17,12 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfemheat.so")
 INCLUDE = os.path.join(ROOT, "include")
 
-SOURCES = ["solver.hip", "engine.hip", "resident_f64.hip", "resident_mixed.hip", "resident_host.cpp", "checks.hip",
-           "server.cpp", "capi.cpp", "tune_cache.cpp"]
+SOURCES = ["solver.hip", "engine.hip", "resident_f64.hip", "resident_mixed.hip", "resident_cheb.hip",
+           "resident_host.cpp", "checks.hip", "server.cpp", "capi.cpp", "tune_cache.cpp"]
 # The resident kernels keep their brick's vectors in register arrays indexed by
 # constants; promoted to vector registers first, the arrays spill.
-EXTRA_FLAGS = {src: ["-mllvm", "-disable-promote-alloca-to-vector"] for src in ("resident_f64.hip", "resident_mixed.hip")}
+EXTRA_FLAGS = {src: ["-mllvm", "-disable-promote-alloca-to-vector"]
+               for src in ("resident_f64.hip", "resident_mixed.hip", "resident_cheb.hip")}
 ARCH = "gfx950"
 
 

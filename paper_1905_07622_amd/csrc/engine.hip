@@ -1344,6 +1344,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     size_t lds = 0;
   };
   std::vector<Launch> launches;
+  const ResForm form = mixed_ ? RES_MIXED : cheb_ ? RES_CHEB : RES_F64;
   std::stable_sort(act.begin(), act.end(), [](const Sim* x, const Sim* y) {
     const fem_heat *p = x->rq.h, *q = y->rq.h;
     return p->kind != q->kind ? p->kind < q->kind : p->res.c < q->res.c;
@@ -1369,7 +1370,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     }
     Launch& l = launches.back();
     l.nthreads = std::max(l.nthreads, sh->res.nthreads);
-    l.lds = std::max(l.lds, res_lds(sh->res.a, sh->res.b, sh->res.c, 8));
+    l.lds = std::max(l.lds, res_lds(sh->res.a, sh->res.b, sh->res.c, form));
     l.blocks += sh->res.nblk;
     nblocks += sh->res.nblk;
     nsteps += (size_t)m;
@@ -1445,6 +1446,18 @@ int Engine::resident_pass(int max_steps, int* advanced) {
       r.E[2] = sh->q64;
       r.EX = sh->r64;
     }
+    if (cheb_) {
+      r.EC[0] = sh->cr64;
+      r.EC[1] = sh->cd64[0];
+      r.EC[2] = sh->cd64[1];
+      r.EC[3] = sh->s64;
+      r.chain = opts_.cheb_degree - 1;
+      r.ch_inv_c = sh->ch_inv_c;
+      for (int c = 0; c < r.chain; ++c) {
+        r.ch_a[c] = sh->ch_a[c];
+        r.ch_b[c] = sh->ch_b[c];
+      }
+    }
     r.F = sh->F64;
     r.pinv64 = sh->pinv64;
     r.lift = sh->lift64;
@@ -1492,9 +1505,9 @@ int Engine::resident_pass(int max_steps, int* advanced) {
   {
     ResidentGate gate(act[0]->rq.h->opts.device, cus, (int)std::min<uint32_t>(want, (uint32_t)cus));
     HIP_TRY(hipMemcpyAsync(st.dev, st.host, o_rec, hipMemcpyHostToDevice, stream_));
-    HIP_TRY(resident_reset(stream_, reinterpret_cast<const ResSim*>(st.dev), (uint32_t)n, mixed_, max_nodes));
+    HIP_TRY(resident_reset(stream_, reinterpret_cast<const ResSim*>(st.dev), (uint32_t)n, form, max_nodes));
     for (const Launch& l : launches)
-      HIP_TRY(resident_launch(mixed_, l.kind, l.planes, l.blocks, l.nthreads, l.lds, stream_,
+      HIP_TRY(resident_launch(form, l.kind, l.planes, l.blocks, l.nthreads, l.lds, stream_,
                               reinterpret_cast<const ResSim*>(st.dev),
                               n == 1 ? nullptr : reinterpret_cast<const uint2*>(st.dev + o_tab) + l.off));
     HIP_TRY(hipMemcpyAsync(st.host + o_out, st.dev + o_out, o_slot - o_out, hipMemcpyDeviceToHost, stream_));

@@ -25,6 +25,12 @@
 // operation (layer_contributions, and the updates below); only the dot
 // products are summed in another grouping (per brick).
 //
+// With the Chebyshev preconditioner P^-1 r is a chain of m - 1 operator
+// applications: its vector takes a second node array in LDS, its residual and
+// sum take registers, and each step is a march and an exchange of the brick's
+// surface without a sum (at 65^3 nodes and m = 3: 45 -> 18.0 us per iteration,
+// four kernels' launches and passes over memory before).
+//
 // Crossing blocks.  Other XCDs' L2s do not see plain stores, so everything
 // that crosses goes through device-scope atomics (loads and stores past the
 // L2s), and no fence is needed:
@@ -42,7 +48,8 @@
 //    sum after it.  The owner puts the marker back once a later sum has shown
 //    that everybody has read; it waits for these stores before it publishes
 //    the next sum that is not an exchange itself, and at least one such sum
-//    lies before the vector's next use.
+//    lies before the vector's next use.  (A vector of the chain is used once
+//    per iteration and cleared behind the iteration's second sum.)
 //
 // Every block of the simulation has to be resident for that.  A launch first
 // meets (rendezvous): blocks count in at one word and wait until all have; a
@@ -560,6 +567,7 @@ struct ResClock {
       } else {
         for (void* E : S.E) gst(static_cast<unsigned long long*>(E), i, ResWord<double>::kEmpty);
         gst(static_cast<unsigned long long*>(S.EX), i, ResWord<double>::kEmpty);
+        for (int c = 0; c < S.chain; ++c) gst(reinterpret_cast<unsigned long long*>(S.EC[c]), i, ResWord<double>::kEmpty);
       }
     }
     for (uint32_t i = tid; i < 2u * kResRep * S.s.nblk * 2u; i += n) gst(S.slots, i, 0ull);
@@ -569,8 +577,10 @@ struct ResClock {
 
 // Steps of one simulation by its blocks.  V: precision of the iterations
 // (double: the FP64 form; float: the mixed form's inner solves); L: planes
-// of a brick; table: block -> (simulation, its brick), nullptr: one simulation.
-template <typename V, int KIND, int L>
+// of a brick; CHEB: P^-1 stands for the Chebyshev preconditioner, a chain of
+// operator applications (FP64); table: block -> (simulation, its brick),
+// nullptr: one simulation.
+template <typename V, int KIND, int L, bool CHEB>
 __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __restrict__ sims,
                                                                const uint2* __restrict__ table) {
   constexpr bool kMixed = sizeof(V) == 4;
@@ -624,6 +634,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
   double* const C64 = D64 + nodes;
   V* const D = reinterpret_cast<V*>(res_smem);
   V* const C = D + nodes;
+  const int chain_at = CHEB ? nodes + 2 * (S.s.a + 1) * (S.s.b + 1) * kResPitch<L> : 0;  // the chain's vector, from D
   double Mc64[8], Kc64[8];
   V Mc[8], Kc[8];
   if constexpr (KIND == kElemBox) {
@@ -694,6 +705,9 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
   bool first = true;      // no iteration yet
   bool fresh = false;     // the last exchange may not have been read by all
   U* stale = nullptr;     // one that has, and is to be cleared
+  // the Chebyshev chain: its step, what it preconditions, its residual and sum
+  int ck = 0, chain_of = 0;
+  V cr[CHEB ? L : 1], y[CHEB ? L : 1];
 
   // T^{n-1} and its halo in D, L's coefficients in C
   auto start_step = [&]() FEM_INLINE {
@@ -728,8 +742,66 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
   };
 
   // What the brick in D is when the operator is applied to it.
-  enum { kRhs, kResidual, kDirection, kReplace };
+  enum { kRhs, kResidual, kDirection, kReplace, kChain };
   int ph = kRhs;
+  // After delta_b: x0 by the guess rule on the brick and its halo, A's coefficients.
+  auto start_solve = [&]() FEM_INLINE {
+    const bool zero = stop_rule == 0 && delta_b == 0.0;
+    auto guess = [&](uint32_t i) FEM_INLINE {
+      const double a = dld(T1, i);
+      double v = S.guess_prev ? a : fma(2.0, a, -dld(T2, i));
+      if (zero) v = (gld(S.pinv64, i) == 0.0) ? a : 0.0;
+      return v;
+    };
+    double* const own64 = column(D64);
+    double v[L], w[kResHalo];
+    cells([&](auto z) FEM_INLINE { v[z] = 0.0; });
+    rows([&](auto z, uint32_t i) FEM_INLINE { v[z] = guess(i); });
+    halo([&](auto k, int) FEM_INLINE { w[k] = ((B.hmask >> k) & 1u) ? guess(B.hnode[k]) : 0.0; });
+    cells([&](auto z) FEM_INLINE {
+      const double t = B.ok ? v[z] : 0.0;
+      if constexpr (kMixed)
+        x64[z] = t;
+      else
+        x[z] = t;
+      own64[z] = t;
+    });
+    halo([&](auto k, int o) FEM_INLINE { D64[o] = w[k]; });
+    if constexpr (!CHEB)
+      fill_coefficients<double, L, false>(B, g, S.s, x0, y0, z0, S.rhoc64, S.k64, S.sa64, S.sbA64, C64);
+    its = sweeps = 0;
+    ph = kResidual;
+  };
+  // A vector of the chain: to its exchange, to the column and its halo
+  // (is_free: the block has read the vector before it).
+  auto chain_vector = [&](int k, bool is_free, const V (&v)[L]) FEM_INLINE {
+    U* const E = reinterpret_cast<U*>(S.EC[k]);
+    put(E, [&](auto z) FEM_INLINE { return v[z]; });
+    if (!is_free) __syncthreads();
+    V* const own = column(D + chain_at);
+    cells([&](auto z) FEM_INLINE { own[z] = v[z]; });
+    V h[kResHalo];
+    halo([&](auto k, int) FEM_INLINE { h[k] = V(0); });
+    meet_halo<V>(M, E, B, h, &lost);
+    halo([&](auto k, int o) FEM_INLINE { D[chain_at + o] = h[k]; });
+  };
+  // d_0 = P^-1 r / c of the chain that preconditions r.
+  auto start_chain = [&]() FEM_INLINE {
+    if constexpr (CHEB) {
+      cells([&](auto z) FEM_INLINE {
+        cr[z] = r[z];
+        y[z] = (p[z] * r[z]) * S.ch_inv_c;
+      });
+      chain_vector(0, true, y);
+      ck = 1;
+      chain_of = ph;
+      ph = kChain;
+    }
+  };
+  // Behind a sum that ends a chain: every block has read the chain's exchanges.
+  auto clear_chain = [&]() FEM_INLINE {
+    for (int k = 0; k < S.chain; ++k) clear_surface<V, L>(B, reinterpret_cast<U*>(S.EC[k]));
+  };
   start_step();
   for (;;) {
     __syncthreads();
@@ -738,8 +810,14 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
       brick_apply<double, KIND, L, kAhead>(B, D64, C64, Mc64, Kc64, acc);
     } else {
       if (timed && ph == kDirection) clk.direction(lead, S.out);
-      brick_apply<V, KIND, L, kAhead>(B, D, C, Mc, Kc, q);
+      brick_apply<V, KIND, L, kAhead>(B, D + (CHEB && ph == kChain ? chain_at : 0), C, Mc, Kc, q);
     }
+    auto prec = [&](auto z) FEM_INLINE -> V {  // P^-1 r
+      if constexpr (CHEB)
+        return y[z];
+      else
+        return p[z] * r[z];
+    };
     auto result = [&](auto z) FEM_INLINE -> double {
       if constexpr (kMixed)
         return acc[z];
@@ -754,41 +832,57 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
         const double bb = fma(fs, gld(S.F, i), result(z));
         if (B.ok) gst(S.b, i, bb);
         const double bh = S.lift ? bb - gld(S.lift, i) : bb;
-        const double t = bh * (gld(S.pinv64, i) * bh);
-        part += B.ok ? t : 0.0;
+        if constexpr (CHEB) {
+          r[z] = B.ok ? bh : 0.0;
+        } else {
+          const double t = bh * (gld(S.pinv64, i) * bh);
+          part += B.ok ? t : 0.0;
+        }
       });
+      if constexpr (CHEB) {  // delta_b in the preconditioner's norm: r holds b - lift for the chain
+        __syncthreads();  // L's coefficients have been read
+        fill_coefficients<double, L, false>(B, g, S.s, x0, y0, z0, S.rhoc64, S.k64, S.sa64, S.sbA64, C64);
+        start_chain();
+        continue;
+      }
       delta_b = plain_sum(part);
       if (uniform(lost)) break;
-      // x0 by the guess rule on the brick and its halo, A's coefficients
-      const bool zero = stop_rule == 0 && delta_b == 0.0;
-      auto guess = [&](uint32_t i) FEM_INLINE {
-        const double a = dld(T1, i);
-        double v = S.guess_prev ? a : fma(2.0, a, -dld(T2, i));
-        if (zero) v = (gld(S.pinv64, i) == 0.0) ? a : 0.0;
-        return v;
-      };
-      double* const own64 = column(D64);
-      double v[L], w[kResHalo];
-      cells([&](auto z) FEM_INLINE { v[z] = 0.0; });
-      rows([&](auto z, uint32_t i) FEM_INLINE { v[z] = guess(i); });
-      halo([&](auto k, int) FEM_INLINE { w[k] = ((B.hmask >> k) & 1u) ? guess(B.hnode[k]) : 0.0; });
-      cells([&](auto z) FEM_INLINE {
-        const double t = B.ok ? v[z] : 0.0;
-        if constexpr (kMixed)
-          x64[z] = t;
-        else
-          x[z] = t;
-        own64[z] = t;
-      });
-      halo([&](auto k, int o) FEM_INLINE { D64[o] = w[k]; });
-      fill_coefficients<double, L, false>(B, g, S.s, x0, y0, z0, S.rhoc64, S.k64, S.sa64, S.sbA64, C64);
-      its = sweeps = 0;
-      ph = kResidual;
+      start_solve();
       continue;
     }
 
     bool finished = false;  // the step's solve has ended
-    if (ph == kResidual) {  // r = b - A x of the initial guess, or after a correction (mixed form)
+    bool chained = false;   // the chain has preconditioned r
+    if (CHEB && ph == kChain) {  // step ck of the chain (EpiCheb's arithmetic)
+      if constexpr (CHEB) {
+        const double a = S.ch_a[ck - 1], b = S.ch_b[ck - 1];
+        V* const own = column(D + chain_at);
+        V d[L];
+        cells([&](auto z) FEM_INLINE {
+          cr[z] = cr[z] - q[z];
+          d[z] = fma(a, own[z], b * (p[z] * cr[z]));
+          y[z] = y[z] + d[z];
+        });
+        if (ck < S.chain) {
+          chain_vector(ck, false, d);
+          ++ck;
+          continue;
+        }
+        ph = chain_of;
+        if (ph == kRhs) {
+          double part = 0.0;
+          cells([&](auto z) FEM_INLINE { part += r[z] * y[z]; });
+          delta_b = plain_sum(part);
+          if (uniform(lost)) break;
+          clear_chain();
+          start_solve();
+          (void)plain_sum(0.0);  // (the chain is used again before the next sum)
+          if (uniform(lost)) break;
+          continue;
+        }
+        chained = true;
+      }
+    } else if (ph == kResidual) {  // r = b - A x of the initial guess, or after a correction (mixed form)
       if constexpr (!kMixed) {
         rows([&](auto z, uint32_t i) FEM_INLINE { r[z] = (here(p[z]) == 0.0) ? 0.0 : gld(S.b, i) - q[z]; });
         rt2 = rtol2;
@@ -885,11 +979,15 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
       });
     }
 
+    if (CHEB && !chained) {
+      start_chain();
+      continue;
+    }
     // r is new: delta = r^T P^-1 r with P^-1 r of the halo, the stop test, the next direction
     if (!finished) {
-      put(E0, [&](auto z) FEM_INLINE { return p[z] * r[z]; });
+      put(E0, [&](auto z) FEM_INLINE { return prec(z); });
       double part = 0.0;
-      cells([&](auto z) FEM_INLINE { part += (double)r[z] * (double)(p[z] * r[z]); });
+      cells([&](auto z) FEM_INLINE { part += (double)r[z] * (double)prec(z); });
       const double now = meet_sum<false, V, true>(M, mlds, part, E0, B, hv, &lost, []() {});
       if (uniform(lost)) break;
       {
@@ -899,6 +997,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
         E2 = t;
         fresh = true;
       }
+      if constexpr (CHEB) clear_chain();
       if (timed && !first) clk.updated(lead, S.out, ph == kReplace);
       if (ph == kReplace) clear_surface<V, L>(B, EX);
       bool done;
@@ -918,13 +1017,13 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
         V* const own = column(D);
         // d = P^-1 r + beta d on the brick and its halo (the first d is P^-1 r)
         if (first) {
-          cells([&](auto z) FEM_INLINE { own[z] = p[z] * r[z]; });
+          cells([&](auto z) FEM_INLINE { own[z] = prec(z); });
           halo([&](auto k, int o) FEM_INLINE { D[o] = hv[k]; });
         } else {  // (all reads before the first write, which could be of the same place for all the compiler knows)
           V v[L], w[kResHalo];
           cells([&](auto z) FEM_INLINE { v[z] = own[z]; });
           halo([&](auto k, int o) FEM_INLINE { w[k] = D[o]; });
-          cells([&](auto z) FEM_INLINE { own[z] = fma(beta, v[z], p[z] * r[z]); });
+          cells([&](auto z) FEM_INLINE { own[z] = fma(beta, v[z], prec(z)); });
           halo([&](auto k, int o) FEM_INLINE { D[o] = fma(beta, w[k], hv[k]); });
         }
         first = false;

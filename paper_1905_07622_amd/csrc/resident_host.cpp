@@ -11,6 +11,7 @@ namespace femheat {
 
 const void* resident_kernel_f64(int kind, int planes);    // resident_f64.hip
 const void* resident_kernel_mixed(int kind, int planes);  // resident_mixed.hip
+const void* resident_kernel_cheb(int kind, int planes);   // resident_cheb.hip
 
 namespace {
 
@@ -43,14 +44,19 @@ std::array<GateState, kMaxDevices>& gates() {
 // 7.8 us, as 49 x 10 x 9 10.3 us; 17^3 as 17 x 6 x 3 6.7 us, in two bricks
 // 11.6 us.  A simulation alone takes the cut with the shortest iteration; a
 // batch member the one with the least iteration time per compute unit, as
-// other members fill the rest.
+// other members fill the rest.  A step of the Chebyshev preconditioner's chain
+// is another march and an exchange without a sum (1.9 us): at degree 3 the
+// resident form takes 18.0 us per iteration on 65^3 nodes (two-kernel form 45),
+// 12.5 us on 21^3 (38.6), 27.4 us on 87 x 87 x 85 (55.8), and every cut that
+// fits is faster than the two-kernel form.
 ResShape resident_shape(const Geom& g, const fem_opts& o, bool batched, int cus) {
   ResShape best{};
   double best_t = 0.0;
-  // the form is Algorithm 1 with the Jacobi preconditioner and two sums per
-  // iteration; a caller that names a gather tile, or another form of the
+  // the form is Algorithm 1 with two sums per iteration, the chain of the
+  // Chebyshev preconditioner as long as its exchange vectors; a caller that names a gather tile, or another form of the
   // iteration, gets the kernels it names
-  if (o.precond != FEM_PRECOND_JACOBI || (o.flags & (FEM_ONE_REDUCTION | FEM_ONE_KERNEL)) || o.tile_x != 0 ||
+  const bool cheb = o.precond == FEM_PRECOND_CHEBYSHEV;
+  if ((cheb && o.cheb_degree - 1 > kResChain) || (o.flags & (FEM_ONE_REDUCTION | FEM_ONE_KERNEL)) || o.tile_x != 0 ||
       o.tile_y != 0 || o.tile_z != 0)
     return best;
   const int limit = std::min(cus, kResBlocks);
@@ -66,13 +72,14 @@ ResShape resident_shape(const Geom& g, const fem_opts& o, bool batched, int cus)
       for (int c : kResPlanes) {
         const int nbz = (g.pz + c - 1) / c;
         const int64_t nblk = (int64_t)nbx * nby * nbz;
-        if (nblk > limit || res_lds(a, b, c, 8) > kResLds) continue;
+        if (nblk > limit || res_lds(a, b, c, cheb ? RES_CHEB : RES_F64) > kResLds) continue;
         const int halo = 2 * (a + 2) * (b + 2) + c * (2 * (a + 2) + 2 * b);
         const int per = (halo + nt - 1) / nt;
         if (per > kResHalo) continue;
         const int xface = nbx > 1 ? 2 * b * c : 0, rest = 2 * (a + 2) * (b + 2) + 2 * (a + 2) * c;
-        const double iter = (nblk > 1 ? 3.8 + 0.0067 * (double)nblk + 0.0045 * xface + 0.0007 * rest : 1.0) +
-                            (c + 1) * (nt <= 256 ? 0.38 : 0.55);
+        const double march = (c + 1) * (nt <= 256 ? 0.38 : 0.55), halo_us = 0.0045 * xface + 0.0007 * rest;
+        double iter = (nblk > 1 ? 3.8 + 0.0067 * (double)nblk + halo_us : 1.0) + march;
+        if (cheb) iter += (o.cheb_degree - 1) * ((nblk > 1 ? 1.9 + halo_us : 0.5) + march);
         const double t = batched ? iter * (double)nblk : iter;
         if (best.nblk == 0 || t < best_t) {
           best = ResShape{a, b, c, nbx, nby, nbz, (uint32_t)nblk, nt};
@@ -92,9 +99,11 @@ bool resident_member(const fem_grid& grid, const fem_opts& o, bool batched, int 
   return resident_shape(g, o, batched, cus).nblk > 0;
 }
 
-hipError_t resident_launch(bool mixed, int kind, int planes, uint32_t blocks, int nthreads, size_t lds,
+hipError_t resident_launch(ResForm form, int kind, int planes, uint32_t blocks, int nthreads, size_t lds,
                            hipStream_t stream, const ResSim* sims, const uint2* table) {
-  const void* fn = mixed ? resident_kernel_mixed(kind, planes) : resident_kernel_f64(kind, planes);
+  const void* fn = form == RES_MIXED  ? resident_kernel_mixed(kind, planes)
+                   : form == RES_CHEB ? resident_kernel_cheb(kind, planes)
+                                      : resident_kernel_f64(kind, planes);
   if (!fn) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

@@ -13,9 +13,9 @@ ResShape resident_shape(const Geom& g, const fem_opts& o, bool batched, int cus)
 
 // One launch over `blocks` bricks of simulations with the same element kind
 // and the same planes per brick.
-hipError_t resident_launch(bool mixed, int kind, int planes, uint32_t blocks, int nthreads, size_t lds,
+hipError_t resident_launch(ResForm form, int kind, int planes, uint32_t blocks, int nthreads, size_t lds,
                            hipStream_t stream, const ResSim* sims, const uint2* table);
-hipError_t resident_reset(hipStream_t stream, const ResSim* sims, uint32_t n, bool mixed, uint32_t max_nodes);
+hipError_t resident_reset(hipStream_t stream, const ResSim* sims, uint32_t n, ResForm form, uint32_t max_nodes);
 
 // Compute units of one device, taken by resident launches of this process:
 // two kernels whose blocks wait for blocks of their own must both fit, or

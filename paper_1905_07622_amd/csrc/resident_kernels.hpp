@@ -5,21 +5,21 @@
 
 namespace femheat {
 
-template <typename V, int KIND>
+template <typename V, int KIND, bool CHEB>
 const void* resident_kernel_planes(int planes) {
   switch (planes) {
-    case 3: return reinterpret_cast<const void*>(&resident_kernel<V, KIND, 3>);
-    case 5: return reinterpret_cast<const void*>(&resident_kernel<V, KIND, 5>);
-    case 9: return reinterpret_cast<const void*>(&resident_kernel<V, KIND, 9>);
+    case 3: return reinterpret_cast<const void*>(&resident_kernel<V, KIND, 3, CHEB>);
+    case 5: return reinterpret_cast<const void*>(&resident_kernel<V, KIND, 5, CHEB>);
+    case 9: return reinterpret_cast<const void*>(&resident_kernel<V, KIND, 9, CHEB>);
     default: return nullptr;
   }
 }
 
-template <typename V>
+template <typename V, bool CHEB>
 const void* resident_kernel_of(int kind, int planes) {
-  return kind == kElemCubic  ? resident_kernel_planes<V, kElemCubic>(planes)
-         : kind == kElemTet6 ? resident_kernel_planes<V, kElemTet6>(planes)
-                             : resident_kernel_planes<V, kElemBox>(planes);
+  return kind == kElemCubic  ? resident_kernel_planes<V, kElemCubic, CHEB>(planes)
+         : kind == kElemTet6 ? resident_kernel_planes<V, kElemTet6, CHEB>(planes)
+                             : resident_kernel_planes<V, kElemBox, CHEB>(planes);
 }
 
 }  // namespace femheat

@@ -28,6 +28,14 @@ struct ResStep {
   double delta, delta_b, tol;
 };
 
+// The kernels: FP64 iterations with the Jacobi or the Chebyshev
+// preconditioner, and the mixed form.
+enum ResForm { RES_F64, RES_MIXED, RES_CHEB };
+
+// Exchange vectors of the Chebyshev chain (the handle's four chain vectors):
+// one per step, so degrees up to 5 run resident.
+constexpr int kResChain = 4;
+
 enum ResState : int32_t { RES_ABSENT = 0, RES_RAN = 1, RES_LOST = 3 };
 
 // What a launch reports per simulation.
@@ -56,6 +64,8 @@ struct ResSim {
   void* E[3];      // exchanged P^-1 r (the iterations' precision), used in turn
   void* EX;        // exchanged iterate of a replacement (the iterations' precision)
   double* EX64;    // mixed form: exchanged FP64 iterate of a correction
+  double* EC[kResChain];  // exchanged vectors of the Chebyshev chain, one per step
+  double ch_inv_c, ch_a[kResChain], ch_b[kResChain];
   void* stash;     // the direction's halo during a replacement: kResHalo values per thread
   unsigned long long* slots;  // 2 sets x kResRep x nblk partials of two words
   unsigned long long* ctl;    // [0] rendezvous, [1] lost
@@ -66,7 +76,7 @@ struct ResSim {
   ResOut* out;
   double rtol2, inner_rtol;
   uint32_t spin_meet, spin;   // polls before a wait gives up
-  int32_t nsens, nsteps, max_iter, stop_rule, R, guess_prev, max_refine, timing;
+  int32_t nsens, nsteps, max_iter, stop_rule, R, guess_prev, max_refine, timing, chain;
 };
 
 // Values of a brick's node array: its columns with the halo, and one column
@@ -74,6 +84,10 @@ struct ResSim {
 __host__ __device__ constexpr int res_nodes(int a, int b, int c) { return (((a + 2) * (b + 2) + 1) * (c + 2) + 3) / 4 * 4; }
 __host__ __device__ constexpr size_t res_lds(int a, int b, int c, size_t w) {
   return w * ((size_t)res_nodes(a, b, c) + 2 * (size_t)(a + 1) * (b + 1) * (c + 2));
+}
+// (the Chebyshev chain's vector is a second node array behind these)
+__host__ __device__ constexpr size_t res_lds(int a, int b, int c, ResForm f) {
+  return res_lds(a, b, c, sizeof(double)) + (f == RES_CHEB ? sizeof(double) * (size_t)res_nodes(a, b, c) : 0);
 }
 
 }  // namespace femheat

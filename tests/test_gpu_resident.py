@@ -57,6 +57,20 @@ def test_cuts_stretched_fp64_locked(gpu, dims):
     assert out["status"] == fh.FEM_OK and rel_l2(out["T_final"], ref["T_final"]) <= GATE64
 
 
+@pytest.mark.parametrize("degree,dims", [(d, c) for c in CUTS[:-1] for d in (2, 3, 5)] + [(3, (86, 86, 84))])
+def test_cuts_chebyshev_locked(gpu, degree, dims):
+    """The preconditioner's chain: one exchange (2), one kept vector (3), all
+    exchange vectors in use (5); the tallest bricks."""
+    p = problem(dims, dt=1e-2, nsteps=1 if dims[2] > 60 else 3)
+    with fh.Heat.from_problem(p, replace_every=4, precond=fh.FEM_PRECOND_CHEBYSHEV, cheb_degree=degree) as h:
+        out = h.run(p.T0, dt=p.dt, theta=p.theta, nsteps=p.nsteps, rtol=p.rtol, save_every=1)
+    ref = oracle.run(p, save_every=1, locked_iters=out["iters"], replace_every=4, nthreads=16,
+                     precond=oracle.PRECOND_CHEBYSHEV, cheb_degree=degree)
+    errs = [rel_l2(out["T_saved"][n], ref["T_saved"][n]) for n in range(p.nsteps)]
+    say(f"  {dims} degree {degree}: iters {list(out['iters'])} rel L2 {max(errs):.1e}")
+    assert out["status"] == fh.FEM_OK and max(errs) <= GATE64
+
+
 @pytest.mark.parametrize("dims", CUTS)
 @pytest.mark.parametrize("max_refine,inner_rtol", [(6, 1e-3), (1, 1e-3)])
 def test_cuts_mixed(gpu, dims, max_refine, inner_rtol):
