@@ -503,22 +503,33 @@ __device__ __forceinline__ void clear_surface(const Brick& B, typename ResWord<V
 template <typename V, int L, bool kRho>
 __device__ inline void fill_coefficients(const Brick& B, const Geom& g, const ResShape& s, int x0, int y0, int z0,
                                          const V* rhoc, const V* kc, V sa, V sb, V* C) {
-  const int cs = B.cw * (s.b + 1), n = (L + 1) * cs;
+  const int cs = B.cw * (s.b + 1);
   const uint32_t ls = (uint32_t)g.nx * (uint32_t)g.ny;
-#pragma unroll 4
-  for (int i = threadIdx.x; i < n; i += s.nthreads) {
-    const int l = i / cs, o = i - l * cs;
+  // a column of elements per thread and round
+  for (int o = here((int)threadIdx.x); o < cs; o += s.nthreads) {
     const int cy = o / B.cw, cx = o - cy * B.cw;
-    const int ex = x0 - 1 + cx, ey = y0 - 1 + cy, ez = z0 - 1 + l;
-    const bool in = ex >= 0 && ex < g.nx && ey >= 0 && ey < g.ny && ez >= 0 && ez < g.nz;
-    const uint32_t e = in ? (uint32_t)ex + (uint32_t)g.nx * (uint32_t)ey + ls * (uint32_t)ez : 0u;
-    const V kk = gld(kc, e);
-    V* p = C + (o * kResPitch<L> + l) * 2;
-    if (kRho) {
-      const V rr = gld(rhoc, e);
-      p[0] = in ? sa * rr : V(0);
-    }
-    p[1] = in ? sb * kk : V(0);
+    const int ex = x0 - 1 + cx, ey = y0 - 1 + cy;
+    const bool in = ex >= 0 && ex < g.nx && ey >= 0 && ey < g.ny;
+    const uint32_t e0 = in ? (uint32_t)ex + (uint32_t)g.nx * (uint32_t)ey : 0u;
+    V* const p = C + o * kResPitch<L> * 2;
+    constexpr int kChunk = L == 9 ? 5 : L + 1;  // layers read at once (registers)
+    each<(L + 1) / kChunk>([&](auto q) FEM_INLINE {
+      V kk[kChunk], rr[kChunk];
+      __builtin_amdgcn_sched_barrier(0);
+      each<kChunk>([&](auto c) FEM_INLINE {
+        const int ez = z0 - 1 + q * kChunk + c;  // (the same in every lane)
+        const uint32_t e = e0 + ls * (uint32_t)min(max(ez, 0), g.nz - 1);
+        kk[c] = gld(kc, e);
+        if constexpr (kRho) rr[c] = gld(rhoc, e);
+      });
+      each<kChunk>([&](auto c) FEM_INLINE {
+        constexpr int l = q * kChunk + c;
+        const int ez = z0 - 1 + l;
+        const bool inside = in && ez >= 0 && ez < g.nz;
+        if constexpr (kRho) p[2 * l] = inside ? sa * rr[c] : V(0);
+        p[2 * l + 1] = inside ? sb * kk[c] : V(0);
+      });
+    });
   }
 }
 
@@ -747,17 +758,25 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
   // After delta_b: x0 by the guess rule on the brick and its halo, A's coefficients.
   auto start_solve = [&]() FEM_INLINE {
     const bool zero = stop_rule == 0 && delta_b == 0.0;
-    auto guess = [&](uint32_t i) FEM_INLINE {
-      const double a = dld(T1, i);
-      double v = S.guess_prev ? a : fma(2.0, a, -dld(T2, i));
-      if (zero) v = (gld(S.pinv64, i) == 0.0) ? a : 0.0;
-      return v;
-    };
     double* const own64 = column(D64);
-    double v[L], w[kResHalo];
-    cells([&](auto z) FEM_INLINE { v[z] = 0.0; });
-    rows([&](auto z, uint32_t i) FEM_INLINE { v[z] = guess(i); });
-    halo([&](auto k, int) FEM_INLINE { w[k] = ((B.hmask >> k) & 1u) ? guess(B.hnode[k]) : 0.0; });
+    // (everything is read before it is used: a branch at each node would wait for each)
+    double v[L], w[kResHalo], v2[L], w2[kResHalo];
+    cells([&](auto z) FEM_INLINE { v[z] = v2[z] = 0.0; });
+    rows([&](auto z, uint32_t i) FEM_INLINE { v[z] = dld(T1, i); });
+    halo([&](auto k, int) FEM_INLINE { w[k] = dld(T1, B.hnode[k]); });
+    if (!S.guess_prev) {
+      rows([&](auto z, uint32_t i) FEM_INLINE { v2[z] = dld(T2, i); });
+      halo([&](auto k, int) FEM_INLINE { w2[k] = dld(T2, B.hnode[k]); });
+    }
+    if (zero) {
+      rows([&](auto z, uint32_t i) FEM_INLINE { v[z] = (gld(S.pinv64, i) == 0.0) ? v[z] : 0.0; });
+      halo([&](auto k, int) FEM_INLINE { w[k] = (gld(S.pinv64, B.hnode[k]) == 0.0) ? w[k] : 0.0; });
+    } else if (!S.guess_prev) {
+      cells([&](auto z) FEM_INLINE { v[z] = fma(2.0, v[z], -v2[z]); });
+      halo([&](auto k, int) FEM_INLINE { w[k] = fma(2.0, w[k], -w2[k]); });
+    }
+    halo([&](auto k, int) FEM_INLINE { w[k] = ((B.hmask >> k) & 1u) ? w[k] : 0.0; });
+    __builtin_amdgcn_sched_barrier(0);
     cells([&](auto z) FEM_INLINE {
       const double t = B.ok ? v[z] : 0.0;
       if constexpr (kMixed)
@@ -919,14 +938,18 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
     if (ph == kRhs) {  // b = L T^{n-1} + dt s F, delta_b
       const double fs = S.fs[m];
       double part = 0.0;
+      double bb[L];
+      rows([&](auto z, uint32_t i) FEM_INLINE { bb[z] = gld(S.F, i); });
       rows([&](auto z, uint32_t i) FEM_INLINE {
-        const double bb = fma(fs, gld(S.F, i), result(z));
-        if (B.ok) gst(S.b, i, bb);
-        const double bh = S.lift ? bb - gld(S.lift, i) : bb;
+        bb[z] = fma(fs, bb[z], result(z));
+        if (B.ok) gst(S.b, i, bb[z]);
+      });
+      if (S.lift) rows([&](auto z, uint32_t i) FEM_INLINE { bb[z] = bb[z] - gld(S.lift, i); });
+      rows([&](auto z, uint32_t i) FEM_INLINE {
         if constexpr (CHEB) {
-          r[z] = B.ok ? bh : 0.0;
+          r[z] = B.ok ? bb[z] : 0.0;
         } else {
-          const double t = bh * (gld(S.pinv64, i) * bh);
+          const double t = bb[z] * (gld(S.pinv64, i) * bb[z]);
           part += B.ok ? t : 0.0;
         }
       });
@@ -975,13 +998,21 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
       }
     } else if (ph == kResidual) {  // r = b - A x of the initial guess, or after a correction (mixed form)
       if constexpr (!kMixed) {
-        rows([&](auto z, uint32_t i) FEM_INLINE { r[z] = (here(p[z]) == 0.0) ? 0.0 : gld(S.b, i) - q[z]; });
+        double bv[L];  // (r is written as a whole: it is not live before)
+        cells([&](auto z) FEM_INLINE { bv[z] = 0.0; });
+        rows([&](auto z, uint32_t i) FEM_INLINE { bv[z] = gld(S.b, i); });
+        cells([&](auto z) FEM_INLINE { r[z] = (here(p[z]) == 0.0) ? 0.0 : bv[z] - q[z]; });
         rt2 = rtol2;
       } else {
-        double part = 0.0;
+        double part = 0.0, pv[L];
+        cells([&](auto z) FEM_INLINE { pv[z] = r64[z] = 0.0; });
         rows([&](auto z, uint32_t i) FEM_INLINE {
-          const double pz = B.ok ? gld(S.pinv64, i) : 0.0;
-          r64[z] = (pz == 0.0) ? 0.0 : gld(S.b, i) - acc[z];
+          pv[z] = gld(S.pinv64, i);
+          r64[z] = gld(S.b, i);
+        });
+        cells([&](auto z) FEM_INLINE {
+          const double pz = B.ok ? pv[z] : 0.0;
+          r64[z] = (pz == 0.0) ? 0.0 : r64[z] - acc[z];
           part += r64[z] * (pz * r64[z]);
         });
         odelta = plain_sum(part);
