@@ -266,9 +266,9 @@ int fem_heat_create(const fem_grid *grid, const double *k_e, const double *rhoc_
  * FEM_ENOCONV (some step hit max_iter: all outputs written, iters = max_iter
  * marks the step) or FEM_EBREAKDOWN (outputs up to the last good step).
  *
- * A simulation whose grid fits on the chip (up to about 1.1 million nodes; the
- * Jacobi preconditioner, no tile override, neither FEM_ONE_REDUCTION nor
- * FEM_ONE_KERNEL) runs in the resident form: one kernel takes many steps, its
+ * A simulation whose grid fits on the chip (up to about 1.1 million nodes with
+ * the Jacobi preconditioner, 0.65 million with Chebyshev of degree 2 to 5; no
+ * tile override, neither FEM_ONE_REDUCTION nor FEM_ONE_KERNEL) runs in the resident form: one kernel takes many steps, its
  * blocks each keep a brick of the grid in LDS and registers and exchange sums
  * and brick surfaces.  The same holds for batch members and served requests.
  * The kernel needs all blocks of a simulation at once: resident launches of one

@@ -11,15 +11,14 @@
 // sweeps of step after step without leaving the kernel.  What crosses blocks
 // is, per iteration, two sums and one layer of P^-1 r around each brick.
 //
-// What bounds it: at 1M nodes (252 bricks of 34 x 15 x 9) 4.9 us of an
-// iteration are the operator's march through LDS (FP64 issue and LDS reads,
-// two waves per SIMD), 2.6 us each of the two sums, and the rest the vector
-// updates and the exchange between them; at 5k nodes (12 bricks) the march
-// takes 1.2 us and a sum 1.3 us, most of it the way of a word from one XCD to
-// the others and back.  Measured per iteration, two-kernel form -> this form
-// (runs of 20-40 steps): 101^3 FP64 28.6 -> 14.0 us, mixed 22.8 -> 13.2 us;
-// 201 x 201 x 26 mixed 21.4 -> 11.7 us; 49^3 FP64 11.8 -> 7.9 us; 17^3 FP64
-// 16.3 -> 6.9 us.
+// What bounds it: at 1M nodes (252 bricks of 34 x 15 x 9) 4.5 us of an
+// iteration are the operator's march through LDS (FP64 issue, two waves per
+// SIMD), 2.3 us each of the two sums, and the rest the vector updates and the
+// exchange between them; at 5k nodes (18 bricks) the march takes 1.0 us and a
+// sum 1.3 us, most of it the way of a word from one XCD to the others and
+// back.  Measured per iteration, two-kernel form -> this form (runs of 20-40
+// steps): 101^3 FP64 28.6 -> 13.5 us, mixed 22.8 -> 12.5 us; 201 x 201 x 26
+// mixed 21.4 -> 10.0 us; 49^3 FP64 11.8 -> 5.9 us; 17^3 FP64 16.3 -> 5.8 us.
 //
 // The arithmetic at a node is that of the two-kernel form, operation by
 // operation (layer_contributions, and the updates below); only the dot
