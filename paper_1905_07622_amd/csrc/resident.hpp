@@ -369,14 +369,8 @@ struct Meet {
   unsigned long long* slots;
   unsigned long long* ctl;
   uint32_t G, blk, seq, spin;
-  int nt;       // threads that work (waves past them have left)
-  bool direct;  // every wave polls every partial
+  int nt;  // threads that work (waves past them have left)
 };
-
-// Polls of a block per round up to which every wave polls for itself (G
-// partials by each wave): it saves a barrier and a pass through LDS per sum,
-// and costs polls, which slow each other down.
-constexpr uint32_t kResDirect = 512;
 
 // Wave sums of a block, zero for waves that have left (two sets alternate),
 // and the waves' shares of the partials.
@@ -390,8 +384,10 @@ struct MeetLds {
 // none).  kWait: earlier stores of the block complete before its partial is
 // published.  gap(): work to do while the partials travel.
 //
-// Few partials (kDirect) are polled and added by every wave for itself;
-// otherwise each wave polls a share of them, and the block adds the shares.
+// Each wave polls a share of the partials, and the block adds the shares: every
+// wave polling all of them saved a barrier and a pass through LDS but added
+// polls, which slow each other down (37^3 nodes 5.85 against 5.45 us per
+// iteration, 25^3 5.10 against 4.90, 17^3 and below equal within 1%).
 template <bool kWait, typename V, bool kHalo, class Gap>
 __device__ __forceinline__ double meet_sum(Meet& M, MeetLds& lds, double v, const typename ResWord<V>::U* E,
                                            const Brick& B, V (&hv)[kResHalo], int* lost, Gap gap) {
@@ -421,7 +417,7 @@ __device__ __forceinline__ double meet_sum(Meet& M, MeetLds& lds, double v, cons
   // leave the fabric to those who still wait (49^3 6.36 -> 5.88 us per
   // iteration, 101^3 13.9 -> 13.5; entry by entry, with a branch for each,
   // 6.07 and 13.6, and a pause between rounds lost more than it gave).
-  const uint32_t first = M.direct ? (uint32_t)lane : (uint32_t)t, step = M.direct ? 64u : (uint32_t)M.nt;
+  const uint32_t first = (uint32_t)t, step = (uint32_t)M.nt;
   double part[kS] = {0.0, 0.0, 0.0, 0.0};
   bool open = kHalo;  // some lane of the wave waits for its halo
   for (uint32_t it = 0;; ++it) {
@@ -463,7 +459,6 @@ __device__ __forceinline__ double meet_sum(Meet& M, MeetLds& lds, double v, cons
     }
   }
   const double x = wave_sum(((part[0] + part[1]) + part[2]) + part[3]);
-  if (M.direct) return x;
   if (lane == 0) lds.all[wid] = x;
   __syncthreads();
   return uniform(sum_of<kW>(lds.all));
@@ -616,8 +611,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
   const ResSim& S = sims[sim];
   const Geom& g = S.g;
   if ((int)threadIdx.x >= S.s.nthreads) return;  // whole waves: the launch's widest brick sets the block
-  Meet M{S.slots, S.ctl, S.s.nblk, blk, 0u, S.spin, S.s.nthreads,
-         S.s.nblk * (uint32_t)(S.s.nthreads / 64) <= kResDirect};
+  Meet M{S.slots, S.ctl, S.s.nblk, blk, 0u, S.spin, S.s.nthreads};
   if (threadIdx.x < kResThreads / 64) mlds.own[0][threadIdx.x] = mlds.own[1][threadIdx.x] = mlds.all[threadIdx.x] = 0.0;
   if (threadIdx.x == 0) {
     lost = 0;
