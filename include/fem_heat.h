@@ -245,6 +245,16 @@ typedef struct {
                                 x/r update (FEM_ONE_KERNEL) */
 } fem_stats;
 
+/* Which form took the time steps of a run (see fem_heat_run), and whether any
+ * simulation had to leave the resident form. */
+typedef struct {
+  int64_t resident_steps;    /* steps taken by resident launches                            */
+  int64_t two_kernel_steps;  /* all others: the two-kernel form, FEM_ONE_REDUCTION, FEM_ONE_KERNEL */
+  int64_t resident_launches; /* resident kernels launched (each takes several steps)        */
+  int64_t unmet;             /* simulations whose blocks did not meet in a resident launch:
+                                they went on in the two-kernel form                         */
+} fem_route;
+
 /* Create a solver for one grid, coefficient field and set of boundary
  * conditions (Sec. 3.2: the element data are prepared once, only the
  * coefficients change between solves).  Validates (FEM_EINVAL): nx,ny,nz >= 1,
@@ -446,6 +456,10 @@ int fem_heat_tune(fem_heat *h, double dt, double theta, uint32_t flags, fem_tune
 
 /* Kernel timing and launch shape of the last run (FEM_TIMING). */
 int fem_heat_stats(const fem_heat *h, fem_stats *out);
+
+/* The route of the handle's last fem_heat_run; with NULL, of the calling
+ * thread's last fem_heat_run_batch, summed over its simulations. */
+int fem_heat_route(const fem_heat *h, fem_route *out);
 
 /* Release a handle (NULL is accepted). */
 void fem_heat_destroy(fem_heat *h);

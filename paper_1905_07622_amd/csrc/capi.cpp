@@ -34,6 +34,7 @@ bool fetch(const double* src, size_t n, bool device, std::vector<double>& out) {
 }
 
 thread_local std::string g_create_error;
+thread_local fem_route g_batch_route;  // of this thread's last fem_heat_run_batch
 
 int check_opts(const fem_opts* opts, fem_opts& o, std::string& why) {
   fem_heat_default_opts(&o);
@@ -229,6 +230,7 @@ int fem_heat_run(fem_heat* h, const double* T0, const double* T_prev, double dt,
 
 int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts, int32_t* status) {
   g_create_error.clear();
+  g_batch_route = fem_route{};
   if (n < 0 || (n > 0 && !reqs)) {
     g_create_error = "reqs and n >= 0 are required";
     return FEM_EINVAL;
@@ -343,6 +345,7 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
   std::vector<std::vector<int32_t>> idx((size_t)G), gst((size_t)G);
   std::vector<int> grc((size_t)G, FEM_OK);
   std::vector<std::string> gerr((size_t)G);
+  std::vector<fem_route> groute((size_t)G);
   try {
     for (int32_t i = 0; i < n && rc == FEM_OK; ++i) {
       const fem_request& r = reqs[i];
@@ -363,7 +366,8 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
           grc[g] = FEM_EDEVICE;
           return;
         }
-        grc[g] = femheat::engine_run(rq[g].data(), (int32_t)rq[g].size(), gs[g], og, gst[g].data(), &gerr[g]);
+        grc[g] = femheat::engine_run(rq[g].data(), (int32_t)rq[g].size(), gs[g], og, gst[g].data(), &gerr[g],
+                                     false, &groute[g]);
       } catch (const std::bad_alloc&) {
         gerr[g] = "host allocation failed";
         grc[g] = FEM_ENOMEM;
@@ -380,6 +384,12 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
         for (int g = 1; g < G; ++g) th.emplace_back(run_group, (size_t)g);
         run_group(0);
         for (auto& t : th) t.join();
+      }
+      for (const fem_route& r : groute) {
+        g_batch_route.resident_steps += r.resident_steps;
+        g_batch_route.two_kernel_steps += r.two_kernel_steps;
+        g_batch_route.resident_launches += r.resident_launches;
+        g_batch_route.unmet += r.unmet;
       }
       for (int g = 0; g < G && rc == FEM_OK; ++g)
         if (grc[(size_t)g] != FEM_OK) {
@@ -575,6 +585,12 @@ void fem_server_destroy(fem_server* s) {
 int fem_heat_stats(const fem_heat* h, fem_stats* out) {
   if (!h || !out) return FEM_EINVAL;
   *out = h->stats;
+  return FEM_OK;
+}
+
+int fem_heat_route(const fem_heat* h, fem_route* out) {
+  if (!out) return FEM_EINVAL;
+  *out = h ? h->route : g_batch_route;
   return FEM_OK;
 }
 

@@ -167,6 +167,7 @@ class Engine {
   void remove(Sim* s);
   std::vector<std::unique_ptr<Sim>>& sims() { return sims_; }
   fem_stats stats{};
+  fem_route route{};
 
  private:
   int compose();
@@ -1251,6 +1252,7 @@ int Engine::finish_step(Sim& s) {
   s.X[1] = spare;
   s.step = n;
   if (s.step >= s.rq.nsteps) s.finished = true;
+  route.two_kernel_steps += 1;
   return FEM_OK;
 }
 
@@ -1285,6 +1287,7 @@ int Engine::write_outputs(Sim& s, float ms) {
 // Takes over what a launch did for one simulation.
 int Engine::resident_result(Sim& s, const ResOut& out, const ResStep* rec) {
   fem_heat* h = s.rq.h;
+  route.resident_steps += out.steps;
   for (int k = 0; k < out.steps; ++k) {
     const ResStep& t = rec[k];
     const int n = s.step;
@@ -1510,6 +1513,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
       HIP_TRY(resident_launch(form, l.kind, l.planes, l.blocks, l.nthreads, l.lds, stream_,
                               reinterpret_cast<const ResSim*>(st.dev),
                               n == 1 ? nullptr : reinterpret_cast<const uint2*>(st.dev + o_tab) + l.off));
+    route.resident_launches += (int64_t)launches.size();
     HIP_TRY(hipMemcpyAsync(st.host + o_out, st.dev + o_out, o_slot - o_out, hipMemcpyDeviceToHost, stream_));
     HIP_TRY(hipStreamSynchronize(stream_));
   }
@@ -1518,6 +1522,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     if (outs[k].state == RES_LOST)
       return fail(h, FEM_EDEVICE, "a block of a resident launch stopped answering the others");
     if (outs[k].state == RES_ABSENT) {  // other work held the device: nothing was done
+      route.unmet += 1;
       RC_TRY(leave_resident(s));
       continue;
     }
@@ -1716,12 +1721,13 @@ int solver_run(fem_heat* h, const double* T0, const double* T_prev, double dt, d
   RunRequest r{h, T0, T_prev, dt, theta, rtol, nsteps, out};
   int32_t st = FEM_OK;
   std::string err;
-  RC_TRY(engine_run(&r, 1, h->stream, h->opts, &st, &err, true));
+  RC_TRY(engine_run(&r, 1, h->stream, h->opts, &st, &err, true, &h->route));
   return st;
 }
 
 int engine_run(const RunRequest* reqs, int32_t n, hipStream_t stream, const fem_opts& opts, int32_t* status,
-               std::string* err, bool one_kernel) {
+               std::string* err, bool one_kernel, fem_route* route) {
+  if (route) *route = fem_route{};
   fem_heat* h = n == 1 ? reqs[0].h : nullptr;
   fem_heat scratch;
   if (!h) h = &scratch;
@@ -1738,6 +1744,7 @@ int engine_run(const RunRequest* reqs, int32_t n, hipStream_t stream, const fem_
     }
   }
   const int rc = e.run();
+  if (route) *route = e.route;
   if (rc != FEM_OK) {
     if (err) *err = h->err;
     return rc;

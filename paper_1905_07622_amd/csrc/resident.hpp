@@ -619,7 +619,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
     if (M.G > 1) {
       __attribute__((address_space(1))) unsigned long long* w =
           (__attribute__((address_space(1))) unsigned long long*)S.ctl;
-      unsigned long long now = __hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1ull;
+      // (a limit of no polls fails every meeting: no block counts in.  Counting
+      // in first, all blocks often had before any of them gave up.)
+      unsigned long long now =
+          S.spin_meet == 0 ? dev_ld(S.ctl, 0)
+                           : __hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1ull;
       for (uint32_t it = 0; !(now & kResAbort) && now < M.G; ++it) {
         if (it >= S.spin_meet) {
           unsigned long long want = now;

@@ -112,6 +112,7 @@ struct fem_heat {
   hipEvent_t ev_apply[2] = {nullptr, nullptr};  // FEM_TIMING: around an apply's operator kernels
 
   fem_stats stats{};
+  fem_route route{};  // of the last run
 
   std::string err;
 };
@@ -134,7 +135,8 @@ void solver_free(fem_heat* h);
 bool resident_member(const fem_grid& g, const fem_opts& o, bool batched, int cus);
 
 // Time stepping (engine.hip): one handle, or a batch of handles advanced
-// together (status[i] receives the outcome of sims[i]).
+// together (status[i] receives the outcome of sims[i]; *route the forms that ran,
+// also when the call fails).
 struct RunRequest {
   fem_heat* h;
   const double* T0;
@@ -146,6 +148,6 @@ struct RunRequest {
 int solver_run(fem_heat* h, const double* T0, const double* T_prev, double dt, double theta, int32_t nsteps,
                double rtol, fem_out* out);
 int engine_run(const RunRequest* reqs, int32_t n, hipStream_t stream, const fem_opts& opts, int32_t* status,
-               std::string* err, bool one_kernel = false);
+               std::string* err, bool one_kernel = false, fem_route* route = nullptr);
 
 }  // namespace femheat

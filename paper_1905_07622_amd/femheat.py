@@ -72,6 +72,11 @@ class fem_stats(ctypes.Structure):
                 ("one_kernel_launches", ctypes.c_int64)]
 
 
+class fem_route(ctypes.Structure):
+    _fields_ = [("resident_steps", ctypes.c_int64), ("two_kernel_steps", ctypes.c_int64),
+                ("resident_launches", ctypes.c_int64), ("unmet", ctypes.c_int64)]
+
+
 FEM_TUNE_BATCH = 0x1
 
 
@@ -114,7 +119,7 @@ class FemError(RuntimeError):
 
 
 EXPORTS = ("fem_heat_create", "fem_heat_run", "fem_heat_apply", "fem_heat_apply_noalloc", "fem_heat_stats",
-           "fem_heat_tune",
+           "fem_heat_route", "fem_heat_tune",
            "fem_heat_destroy",
            "fem_heat_default_opts", "fem_strerror", "fem_last_error", "fem_heat_run_batch",
            "fem_server_create", "fem_server_submit", "fem_server_poll", "fem_server_wait", "fem_server_cancel",
@@ -138,6 +143,7 @@ def lib():
         L.fem_heat_apply.argtypes = [vp, ctypes.c_int32, ctypes.c_double, ctypes.c_double, _dp, _dp]
         L.fem_heat_apply_noalloc.argtypes = [vp, ctypes.c_int32, ctypes.c_double, ctypes.c_double, vp, vp]
         L.fem_heat_stats.argtypes = [vp, ctypes.POINTER(fem_stats)]
+        L.fem_heat_route.argtypes = [vp, ctypes.POINTER(fem_route)]
         L.fem_heat_tune.argtypes = [vp, ctypes.c_double, ctypes.c_double, ctypes.c_uint32,
                                     ctypes.POINTER(fem_tune_result)]
         L.fem_heat_run_batch.argtypes = [ctypes.POINTER(fem_request), ctypes.c_int32, ctypes.POINTER(fem_opts), _ip]
@@ -162,7 +168,7 @@ def lib():
         L.fem_last_error.argtypes = [vp]
         L.fem_last_error.restype = ctypes.c_char_p
         for n in ("fem_heat_create", "fem_heat_run", "fem_heat_apply", "fem_heat_apply_noalloc", "fem_heat_stats",
-                  "fem_heat_tune"):
+                  "fem_heat_route", "fem_heat_tune"):
             getattr(L, n).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -220,6 +226,15 @@ def fem_heat_stats(h) -> fem_stats:
     if st != FEM_OK:
         raise FemError(st, "fem_heat_stats")
     return s
+
+
+def fem_heat_route(h) -> fem_route:
+    """The forms that took the steps of a handle's last run (None: of this thread's last batch)."""
+    r = fem_route()
+    st = lib().fem_heat_route(h, ctypes.byref(r))
+    if st != FEM_OK:
+        raise FemError(st, "fem_heat_route")
+    return r
 
 
 def fem_heat_destroy(h) -> None:
@@ -401,6 +416,12 @@ def run_batch(problems, *, save_every=0, sensors=False, T_prev=None, check=True,
     return st, results
 
 
+def batch_route() -> dict:
+    """The forms that took the steps of this thread's last run_batch, summed over its simulations."""
+    r = fem_heat_route(None)
+    return {k: getattr(r, k) for k, _ in fem_route._fields_}
+
+
 def _status_dict(st: fem_status) -> dict:
     return {k: getattr(st, k) for k, _ in fem_status._fields_}
 
@@ -579,6 +600,11 @@ class Heat:
     def stats(self) -> dict:
         s = fem_heat_stats(self.h)
         return {k: getattr(s, k) for k, _ in fem_stats._fields_}
+
+    def route(self) -> dict:
+        """The forms that took the steps of the last run (fem_heat_route)."""
+        r = fem_heat_route(self.h)
+        return {k: getattr(r, k) for k, _ in fem_route._fields_}
 
     def close(self):
         if self.h:
