@@ -1355,7 +1355,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
   const size_t n = act.size();
   std::vector<int> steps(n);
   std::vector<size_t> slot(n);
-  size_t nsteps = 0, nblocks = 0, nslots = 0;
+  size_t nsteps = 0, nblocks = 0, nslots = 2;  // (the first words: the launches' own)
   uint32_t max_nodes = 0;
   for (size_t k = 0; k < n; ++k) {
     const Sim& s = *act[k];
@@ -1470,6 +1470,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     r.T[2] = s.X[0];
     unsigned long long* words = reinterpret_cast<unsigned long long*>(st.dev + o_slot) + slot[k];
     r.ctl = words;
+    r.running = reinterpret_cast<unsigned long long*>(st.dev + o_slot);
     r.slots = words + 2;
     r.stash = r.slots + (size_t)2 * kResRep * sh->res.nblk * 2;
     r.fs = reinterpret_cast<const double*>(st.dev + o_fs) + at;
@@ -1480,7 +1481,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     r.traces = s.nsens > 0 ? sh->traces_dev + (size_t)s.step * s.nsens : nullptr;
     r.rtol2 = s.rq.rtol * s.rq.rtol;
     r.inner_rtol = opts_.inner_rtol;
-    r.spin_meet = meet_limit >= 0 ? (uint32_t)meet_limit : nblocks > (size_t)sh->cus ? kResMeetQueued : kResMeet;
+    r.spin_meet = meet_limit >= 0 ? (uint32_t)meet_limit : kResMeet;
     r.spin = kResSpin;
     r.nsteps = steps[k];
     r.max_iter = opts_.max_iter;

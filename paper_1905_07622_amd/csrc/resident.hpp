@@ -54,9 +54,13 @@
 // meets (rendezvous): blocks count in at one word and wait until all have; a
 // block whose wait runs out marks the word, which succeeds only while the
 // count is incomplete, and then no block proceeds.  Nothing has been written
-// by then, so the host launches again or takes the two-kernel form.  After
-// the meeting every wait is for a block that runs, and the bound on it only
-// guards against the impossible.
+// by then, so the host takes the two-kernel form.  The blocks of a launch may
+// outnumber the compute units: those of a later simulation then wait for an
+// earlier one to end, and the time that one runs does not count.  (It ends by
+// itself.  With a long bound instead, two processes whose launches each held
+// part of the device stood still for all of it.)  After the meeting every wait
+// is for a block that runs, and the bound on it only guards against the
+// impossible.
 #pragma once
 
 #include <utility>
@@ -93,7 +97,18 @@ __device__ __forceinline__ void dev_st(U* base, uint32_t i, U v) {
   gptr<char> b = (gptr<char>)base;
   __hip_atomic_store((gptr<U>)(b + (uint32_t)(i * (uint32_t)sizeof(U))), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// base[i] += v; what it becomes
+template <typename U>
+__device__ __forceinline__ U dev_add(U* base, uint32_t i, U v) {
+  gptr<char> b = (gptr<char>)base;
+  return __hip_atomic_fetch_add((gptr<U>)(b + (uint32_t)(i * (uint32_t)sizeof(U))), v, __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT) + v;
+}
 #else
+template <typename U>
+__device__ U dev_add(U* base, uint32_t i, U v) {
+  return base[i] += v;
+}
 template <typename U>
 __device__ U dev_ld(const U* base, uint32_t i) {
   return base[i];
@@ -586,6 +601,7 @@ struct ResClock {
     for (uint32_t i = tid; i < 2u * kResRep * S.s.nblk * 2u; i += n) gst(S.slots, i, 0ull);
   }
   if (tid < 2) gst(S.ctl, tid, 0ull);
+  if (blockIdx.y == 0 && tid == 0) gst(S.running, 0u, 0ull);
 }
 
 // Steps of one simulation by its blocks.  V: precision of the iterations
@@ -616,15 +632,16 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
   if (threadIdx.x == 0) {
     lost = 0;
     go = 1;
+    bool all = M.G == 1;  // this block completes the meeting
     if (M.G > 1) {
       __attribute__((address_space(1))) unsigned long long* w =
           (__attribute__((address_space(1))) unsigned long long*)S.ctl;
       // (a limit of no polls fails every meeting: no block counts in.  Counting
       // in first, all blocks often had before any of them gave up.)
-      unsigned long long now =
-          S.spin_meet == 0 ? dev_ld(S.ctl, 0)
-                           : __hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1ull;
+      unsigned long long now = S.spin_meet == 0 ? dev_ld(S.ctl, 0) : dev_add(S.ctl, 0, 1ull);
+      all = now == M.G;
       for (uint32_t it = 0; !(now & kResAbort) && now < M.G; ++it) {
+        if ((it & 63u) == 63u && dev_ld(S.running, 0) != 0) it = 0;
         if (it >= S.spin_meet) {
           unsigned long long want = now;
           if (__hip_atomic_compare_exchange_strong(w, &want, now | kResAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -638,6 +655,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
       }
       if (now & kResAbort) go = 0;
     }
+    if (all) (void)dev_add(S.running, 0, 1ull);
   }
   __syncthreads();
   if (!uniform(go)) return;
@@ -1166,6 +1184,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
   }
   if (lost && threadIdx.x == 0) dev_st(S.ctl, 1, 1ull);  // the others give up too
   if (lead) {
+    (void)dev_add(S.running, 0, ~0ull);
     ResOut& w = *S.out;
     w.state = lost ? RES_LOST : RES_RAN;
     w.steps = m;

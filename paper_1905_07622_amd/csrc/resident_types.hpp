@@ -13,10 +13,9 @@ constexpr int kResHalo = 5;        // most halo nodes per thread
 constexpr int kResRep = 8;         // copies of each partial
 constexpr size_t kResLds = 160 * 1024 - 1024;  // dynamic LDS of a block (the rest: sums and flags)
 
-// Polls before a wait gives up (about 0.7 us each).  The meeting: 20 ms; in a
-// launch with more blocks than compute units, where the blocks of a later
-// simulation wait for an earlier one's to end, 20 s.  Any other wait: 2 s.
-constexpr uint32_t kResMeet = 30000, kResMeetQueued = 30000000, kResSpin = 3000000;
+// Polls before a wait gives up (about 0.7 us each).  The meeting: 20 ms in
+// which no simulation of the launch runs.  Any other wait: 2 s.
+constexpr uint32_t kResMeet = 30000, kResSpin = 3000000;
 
 // Steps per launch of a run, and of a server's epoch (which takes
 // cancellations and admissions in between).
@@ -69,6 +68,7 @@ struct ResSim {
   void* stash;     // the direction's halo during a replacement: kResHalo values per thread
   unsigned long long* slots;  // 2 sets x kResRep x nblk partials of two words
   unsigned long long* ctl;    // [0] rendezvous, [1] lost
+  unsigned long long* running;  // of the launch: its simulations that have met and not ended
   const double* fs;           // dt * s_n of the launch's steps
   ResStep* rec;               // of the launch's steps
   const double* xyz;
