@@ -82,6 +82,7 @@ struct Sim {
   bool sweeping = false, broke = false;
   Scalars so{}, si{};  // latest settled outer and inner state
   bool resident = false;             // advances in resident launches
+  uint64_t turn = 0;                 // the resident pass that it last took part in
   uint64_t res_count[2] = {0, 0};    // its iterations and replacements so far (timing samples)
 };
 
@@ -162,7 +163,7 @@ class Engine {
     p = nullptr;
   }
   int run();
-  int step(int* active, int resident_steps);
+  int step(int* active, const ResBounds& bounds);
   int write_outputs(Sim& s, float ms);
   void remove(Sim* s);
   std::vector<std::unique_ptr<Sim>>& sims() { return sims_; }
@@ -201,10 +202,12 @@ class Engine {
   template <typename V>
   int pcg(int first_chunk);
   int epoch();
-  int resident_pass(int max_steps, int* advanced);
+  int resident_pass(const ResBounds& bounds, int* advanced);
   int resident_result(Sim& s, const ResOut& out, const ResStep* rec);
   int leave_resident(Sim& s);
   ResStage own_stage_;       // buffers of resident launches
+  uint64_t passes_ = 0;
+  int wall_khz_ = 0;  // rate of the device clock, once asked
   bool keep_stage_ = false;  // a run of one handle: they stay with the handle
   int mixed_sweeps();
   int finish_step(Sim& s);
@@ -1315,9 +1318,7 @@ int Engine::resident_result(Sim& s, const ResOut& out, const ResStep* rec) {
   if (out.steps > 0 && o && o->T_saved && o->save_every > 0 && s.step % o->save_every == 0)
     RC_TRY(copy_out(h, o->T_saved + (size_t)(s.step / o->save_every - 1) * h->g.N, s.T1, (size_t)h->g.N * sizeof(double)));
   if (timing_) {
-    int khz = 0;
-    HIP_TRY(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, h->opts.device));
-    const double ms = 1.0 / std::max(khz, 1);
+    const double ms = 1.0 / std::max(wall_khz_, 1);
     stats.gather_launches += (int64_t)out.samples[0];
     stats.gather_ms += (double)out.ticks[0] * ms;
     stats.update_launches += (int64_t)out.samples[1];
@@ -1330,10 +1331,11 @@ int Engine::resident_result(Sim& s, const ResOut& out, const ResStep* rec) {
   return FEM_OK;
 }
 
-// Advances every resident simulation by up to max_steps steps (fewer at the
-// end of its run and at a step whose field is saved): one launch per element
-// kind and brick height.  *advanced receives how many took part.
-int Engine::resident_pass(int max_steps, int* advanced) {
+// Advances every resident simulation by some steps (at most as bounded, fewer
+// at the end of its run and at a step whose field is saved; none where the
+// launch's time is over before its turn): one launch per element kind and
+// brick height.  *advanced receives how many simulations there were.
+int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
   fem_heat* h = h_;
   *advanced = 0;
   std::vector<Sim*> act;
@@ -1350,17 +1352,20 @@ int Engine::resident_pass(int max_steps, int* advanced) {
   const ResForm form = mixed_ ? RES_MIXED : cheb_ ? RES_CHEB : RES_F64;
   std::stable_sort(act.begin(), act.end(), [](const Sim* x, const Sim* y) {
     const fem_heat *p = x->rq.h, *q = y->rq.h;
-    return p->kind != q->kind ? p->kind < q->kind : p->res.c < q->res.c;
+    if (p->kind != q->kind) return p->kind < q->kind;
+    if (p->res.c != q->res.c) return p->res.c < q->res.c;
+    return x->turn < y->turn;  // those that the last launch had no time for go first
   });
   const size_t n = act.size();
   std::vector<int> steps(n);
   std::vector<size_t> slot(n);
+  std::vector<char> first(n, 0);  // of its launch
   size_t nsteps = 0, nblocks = 0, nslots = 2;  // (the first words: the launches' own)
   uint32_t max_nodes = 0;
   for (size_t k = 0; k < n; ++k) {
     const Sim& s = *act[k];
     const fem_heat* sh = s.rq.h;
-    int m = std::min(max_steps, s.rq.nsteps - s.step);
+    int m = std::min(bounds.steps, s.rq.nsteps - s.step);
     const fem_out* o = s.rq.out;
     if (o && o->T_saved && o->save_every > 0) m = std::min(m, o->save_every - s.step % o->save_every);
     steps[k] = m;
@@ -1370,6 +1375,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
       l.planes = sh->res.c;
       l.off = (uint32_t)nblocks;
       launches.push_back(l);
+      first[k] = 1;
     }
     Launch& l = launches.back();
     l.nthreads = std::max(l.nthreads, sh->res.nthreads);
@@ -1408,6 +1414,10 @@ int Engine::resident_pass(int max_steps, int* advanced) {
   std::vector<size_t> rec_at(n);
   long meet_limit = -1;  // tests of a launch whose blocks do not meet
   if (const char* v = std::getenv("FEMHEAT_RESIDENT_MEET_LIMIT")) meet_limit = std::strtol(v, nullptr, 10);
+  double hold_ms = bounds.ms;  // tests of short launches
+  if (const char* v = std::getenv("FEMHEAT_RESIDENT_LAUNCH_MS")) hold_ms = std::strtod(v, nullptr);
+  if (wall_khz_ == 0)
+    HIP_TRY(hipDeviceGetAttribute(&wall_khz_, hipDeviceAttributeWallClockRate, act[0]->rq.h->opts.device));
   for (size_t k = 0; k < n; ++k) {
     Sim& s = *act[k];
     const fem_heat* sh = s.rq.h;
@@ -1470,7 +1480,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     r.T[2] = s.X[0];
     unsigned long long* words = reinterpret_cast<unsigned long long*>(st.dev + o_slot) + slot[k];
     r.ctl = words;
-    r.running = reinterpret_cast<unsigned long long*>(st.dev + o_slot);
+    r.launch = reinterpret_cast<unsigned long long*>(st.dev + o_slot);
     r.slots = words + 2;
     r.stash = r.slots + (size_t)2 * kResRep * sh->res.nblk * 2;
     r.fs = reinterpret_cast<const double*>(st.dev + o_fs) + at;
@@ -1482,6 +1492,8 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     r.rtol2 = s.rq.rtol * s.rq.rtol;
     r.inner_rtol = opts_.inner_rtol;
     r.spin_meet = meet_limit >= 0 ? (uint32_t)meet_limit : kResMeet;
+    r.queued = first[k] ? 0 : 1;
+    r.hold = (uint64_t)(std::max(hold_ms, 0.0) * wall_khz_);
     r.spin = kResSpin;
     r.nsteps = steps[k];
     r.max_iter = opts_.max_iter;
@@ -1496,8 +1508,7 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     out.count[1] = s.res_count[1];
     rec_at[k] = at;
     for (int q = 0; q < steps[k]; ++q) fs[at++] = dt * schedule_value(sh, (int64_t)s.first + s.step + q + 1);
-    const uint32_t first = (uint32_t)k;
-    for (uint32_t b = 0; b < sh->res.nblk; ++b) tab[bt++] = make_uint2(first, b);
+    for (uint32_t b = 0; b < sh->res.nblk; ++b) tab[bt++] = make_uint2((uint32_t)k, b);
   }
   // The launch may have to wait for compute units while it holds some: what
   // this stream was given before (by a caller, perhaps behind other work)
@@ -1518,8 +1529,11 @@ int Engine::resident_pass(int max_steps, int* advanced) {
     HIP_TRY(hipMemcpyAsync(st.host + o_out, st.dev + o_out, o_slot - o_out, hipMemcpyDeviceToHost, stream_));
     HIP_TRY(hipStreamSynchronize(stream_));
   }
+  ++passes_;
   for (size_t k = 0; k < n; ++k) {
     Sim& s = *act[k];
+    if (outs[k].state == RES_LATE) continue;
+    s.turn = passes_;
     if (outs[k].state == RES_LOST)
       return fail(h, FEM_EDEVICE, "a block of a resident launch stopped answering the others");
     if (outs[k].state == RES_ABSENT) {  // other work held the device: nothing was done
@@ -1534,11 +1548,12 @@ int Engine::resident_pass(int max_steps, int* advanced) {
 }
 
 // One epoch: every simulation that still has steps advances by one step (in
-// the resident form by up to resident_steps).  *active receives how many took
-// part (0: nothing left to do).
-int Engine::step(int* active, int resident_steps) {
+// the resident form by one or more, within the bounds, or by none if the
+// launch's time is over before its turn).  *active receives how many had steps
+// left (0: nothing left to do).
+int Engine::step(int* active, const ResBounds& bounds) {
   int advanced = 0;
-  RC_TRY(resident_pass(resident_steps, &advanced));
+  RC_TRY(resident_pass(bounds, &advanced));
   bool others = false;
   for (auto& sp : sims_) others = others || (!sp->finished && !sp->resident);
   *active = advanced;
@@ -1555,7 +1570,7 @@ int Engine::run() {
   HIP_TRY(hipEventRecord(ev_run_[0], stream_));
   for (;;) {
     int active = 0;
-    RC_TRY(step(&active, kResRunSteps));
+    RC_TRY(step(&active, kResRun));
     if (active == 0) break;
   }
   HIP_TRY(hipEventRecord(ev_run_[1], stream_));
@@ -1705,7 +1720,7 @@ int engine_tune(fem_heat* h, double dt, double theta, uint32_t flags, fem_tune_r
 Engine* engine_new(hipStream_t stream, const fem_opts& opts, fem_heat* err) { return new Engine(stream, opts, err); }
 void engine_delete(Engine* e) { delete e; }
 int engine_add(Engine* e, const RunRequest& r, Sim** out) { return e->add(r, out); }
-int engine_step(Engine* e, int* active) { return e->step(active, kResServeSteps); }
+int engine_step(Engine* e, int* active) { return e->step(active, kResServe); }
 bool engine_sim_finished(const Sim* s) { return s->finished; }
 int engine_sim_status(const Sim* s) { return s->status; }
 int32_t engine_sim_steps(const Sim* s) { return s->step; }

@@ -54,7 +54,9 @@
 // meets (rendezvous): blocks count in at one word and wait until all have; a
 // block whose wait runs out marks the word, which succeeds only while the
 // count is incomplete, and then no block proceeds.  Nothing has been written
-// by then, so the host takes the two-kernel form.  The blocks of a launch may
+// by then, so the host takes the two-kernel form.  (A block that comes after
+// the launch's time is over does not count in, and marks the word too: the
+// simulation waits for the next launch.)  The blocks of a launch may
 // outnumber the compute units: those of a later simulation then wait for an
 // earlier one to end, and the time that one runs does not count.  (It ends by
 // itself.  With a long bound instead, two processes whose launches each held
@@ -582,7 +584,8 @@ struct ResClock {
 };
 
 // Puts the marker into the exchange vectors of every simulation of a launch
-// and clears its slots and words (blockIdx.y: simulation).
+// and clears its slots and words (blockIdx.y: simulation); the launch's own
+// words count from here.
 [[maybe_unused]] static __global__ void __launch_bounds__(256) resident_reset_kernel(const ResSim* sims, int mixed) {
   const ResSim& S = sims[blockIdx.y];
   const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, n = gridDim.x * blockDim.x, N = S.g.N;
@@ -601,7 +604,10 @@ struct ResClock {
     for (uint32_t i = tid; i < 2u * kResRep * S.s.nblk * 2u; i += n) gst(S.slots, i, 0ull);
   }
   if (tid < 2) gst(S.ctl, tid, 0ull);
-  if (blockIdx.y == 0 && tid == 0) gst(S.running, 0u, 0ull);
+  if (blockIdx.y == 0 && tid == 0) {
+    gst(S.launch, 0u, 0ull);
+    gst(S.launch, 1u, (unsigned long long)wall_clock64());
+  }
 }
 
 // Steps of one simulation by its blocks.  V: precision of the iterations
@@ -617,6 +623,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
   extern __shared__ __align__(16) unsigned char res_smem[];
   __shared__ int lost, go;
   __shared__ ResClock clk;
+  __shared__ uint64_t until;  // (of the lead block) the device clock at which the launch is to end
   __shared__ __align__(16) MeetLds mlds;
   uint32_t sim = 0, blk = blockIdx.x;
   if (table) {
@@ -633,16 +640,20 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
     lost = 0;
     go = 1;
     bool all = M.G == 1;  // this block completes the meeting
+    until = gld(S.launch, 1u) + S.hold;
+    const bool late = S.queued && wall_clock64() > until;  // no turn in this launch
+    if (late) S.out->state = RES_LATE;
     if (M.G > 1) {
       __attribute__((address_space(1))) unsigned long long* w =
           (__attribute__((address_space(1))) unsigned long long*)S.ctl;
+      const uint32_t limit = late ? 0u : S.spin_meet;
       // (a limit of no polls fails every meeting: no block counts in.  Counting
       // in first, all blocks often had before any of them gave up.)
-      unsigned long long now = S.spin_meet == 0 ? dev_ld(S.ctl, 0) : dev_add(S.ctl, 0, 1ull);
+      unsigned long long now = limit == 0 ? dev_ld(S.ctl, 0) : dev_add(S.ctl, 0, 1ull);
       all = now == M.G;
       for (uint32_t it = 0; !(now & kResAbort) && now < M.G; ++it) {
-        if ((it & 63u) == 63u && dev_ld(S.running, 0) != 0) it = 0;
-        if (it >= S.spin_meet) {
+        if ((it & 63u) == 63u && dev_ld(S.launch, 0) != 0) it = 0;
+        if (it >= limit) {
           unsigned long long want = now;
           if (__hip_atomic_compare_exchange_strong(w, &want, now | kResAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT))
@@ -654,8 +665,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
         }
       }
       if (now & kResAbort) go = 0;
+    } else if (late) {
+      go = 0;
+      all = false;
     }
-    if (all) (void)dev_add(S.running, 0, 1ull);
+    if (all) (void)dev_add(S.launch, 0, 1ull);
   }
   __syncthreads();
   if (!uniform(go)) return;
@@ -1166,8 +1180,9 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
       T1 = t;
     }
     ++m;
+    bool over = false;
     if (m < S.nsteps || S.nsens > 0) {
-      (void)plain_sum(0.0);
+      over = plain_sum(lead && wall_clock64() > until ? 1.0 : 0.0) != 0.0;
       if (uniform(lost)) {
         --m;
         break;
@@ -1178,13 +1193,13 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
       for (int s = first_q; s < S.nsens; s += stride)
         S.traces[(size_t)(m - 1) * S.nsens + s] = sensor_value(g, S.xyz, s, [&](uint32_t i) FEM_INLINE { return dld(T1, i); });
     }
-    if (m >= S.nsteps) break;
+    if (m >= S.nsteps || over) break;
     ph = kRhs;
     start_step();
   }
   if (lost && threadIdx.x == 0) dev_st(S.ctl, 1, 1ull);  // the others give up too
   if (lead) {
-    (void)dev_add(S.running, 0, ~0ull);
+    (void)dev_add(S.launch, 0, ~0ull);
     ResOut& w = *S.out;
     w.state = lost ? RES_LOST : RES_RAN;
     w.steps = m;

@@ -17,9 +17,22 @@ constexpr size_t kResLds = 160 * 1024 - 1024;  // dynamic LDS of a block (the re
 // which no simulation of the launch runs.  Any other wait: 2 s.
 constexpr uint32_t kResMeet = 30000, kResSpin = 3000000;
 
-// Steps per launch of a run, and of a server's epoch (which takes
-// cancellations and admissions in between).
-constexpr int kResRunSteps = 128, kResServeSteps = 4;
+// What a launch does before it gives its compute units back: that many steps
+// of a simulation, or fewer once it has lasted that long: its simulations then
+// end at the end of the step they are in, and those whose turn has not come
+// begin the next launch.  Other work on the device waits for a launch as a
+// whole (a run of 1M nodes leaves it four compute units), and a server takes
+// cancellations and admissions between launches, so its bounds are shorter.
+// Measured on a server, requests of 17^3 nodes and 5 steps, one at a time,
+// beside four of 97^3 (mixed): median latency 29.0 ms with 4 steps and no time
+// bound, 11.1 ms with 4 steps and 2 ms, 8.7 ms with 16 steps and 2 ms, 15.3 ms
+// with 3 ms for the large and 1 ms for the small; the four took 505, 546, 561
+// and 530 ms, ten mixed requests without a steady load 71, 73, 75 and 72 ms.
+struct ResBounds {
+  int steps;
+  double ms;
+};
+constexpr ResBounds kResRun{128, 100.0}, kResServe{4, 2.0};
 
 // What a step reports.
 struct ResStep {
@@ -35,11 +48,12 @@ enum ResForm { RES_F64, RES_MIXED, RES_CHEB };
 // one per step, so degrees up to 5 run resident.
 constexpr int kResChain = 4;
 
-enum ResState : int32_t { RES_ABSENT = 0, RES_RAN = 1, RES_LOST = 3 };
+enum ResState : int32_t { RES_ABSENT = 0, RES_RAN = 1, RES_LATE = 2, RES_LOST = 3 };
 
 // What a launch reports per simulation.
 struct ResOut {
-  int32_t state;   // RES_ABSENT: not every block was resident in time, nothing was done
+  int32_t state;   // RES_ABSENT: not every block was resident in time, nothing was done; RES_LATE: the launch's
+                   // time was over before the simulation's turn, nothing was done
   int32_t steps;   // steps completed
   int32_t status;  // 0 or kStatusBreakdown (in the step after the completed ones)
   int32_t pad;
@@ -68,7 +82,7 @@ struct ResSim {
   void* stash;     // the direction's halo during a replacement: kResHalo values per thread
   unsigned long long* slots;  // 2 sets x kResRep x nblk partials of two words
   unsigned long long* ctl;    // [0] rendezvous, [1] lost
-  unsigned long long* running;  // of the launch: its simulations that have met and not ended
+  unsigned long long* launch; // of the launch: [0] simulations that have met and not ended, [1] its start (device clock)
   const double* fs;           // dt * s_n of the launch's steps
   ResStep* rec;               // of the launch's steps
   const double* xyz;
@@ -77,6 +91,9 @@ struct ResSim {
   double rtol2, inner_rtol;
   uint32_t spin_meet, spin;   // polls before a wait gives up
   int32_t nsens, nsteps, max_iter, stop_rule, R, guess_prev, max_refine, timing, chain;
+  // (last: ahead of the vectors these moved the kernels' scalar loads, 1.5% on a 201 x 201 x 26 mixed run)
+  int32_t queued;             // not the first simulation of its launch (which always runs)
+  uint64_t hold;              // device clock ticks that the launch lasts at most
 };
 
 // Values of a brick's node array: its columns with the halo, and one column

@@ -3,6 +3,7 @@ that wait for compute units, and work that waits for theirs."""
 import ctypes
 import time
 
+import numpy as np
 import pytest
 
 from oracle import oracle
@@ -52,3 +53,65 @@ def test_a_launch_that_cannot_have_its_compute_units_gives_up_soon(gpu, members)
     assert secs < 5.0
     for p, o in zip(probs, res):
         assert rel_l2(o["T_final"], oracle.run(p, locked_iters=o["iters"], nthreads=8)["T_final"]) <= GATE64
+
+
+def same_bits(a, b):
+    for key in ("T_final", "T_saved", "traces", "iters", "relres", "refine_sweeps"):
+        assert (a[key] is None) == (b[key] is None)
+        assert a[key] is None or np.array_equal(a[key], b[key]), key
+
+
+@pytest.mark.parametrize("dims", [(6, 5, 2), (16, 16, 17), (47, 53, 26)])
+@pytest.mark.parametrize("opts", [{}, dict(precision=fh.FEM_FP32_FP64DOT), dict(precond=fh.FEM_PRECOND_CHEBYSHEV)])
+def test_short_launches_change_no_bits(gpu, monkeypatch, opts, dims):
+    """A launch that may hold its compute units for no time at all (set from
+    the host) ends after one step: as many launches as steps, and the same
+    fields, counts and traces as from one launch.  One brick and many; fields
+    saved and not."""
+    p = wl.random_problem(*dims, seed=21, nsteps=7, rtol=1e-9)
+    xyz = np.random.default_rng(4).uniform(0, 1, (5, 3)) * [p.nx * p.hx, p.ny * p.hy, p.nz * p.hz]
+    for save_every in (0, 3):
+        kw = dict(dt=p.dt, theta=p.theta, nsteps=p.nsteps, rtol=p.rtol, sensors=xyz, save_every=save_every)
+        with fh.Heat.from_problem(p, **opts) as h:
+            one = h.run(p.T0, **kw)
+            assert h.route()["resident_launches"] == (3 if save_every else 1)
+            monkeypatch.setenv("FEMHEAT_RESIDENT_LAUNCH_MS", "0")
+            each = h.run(p.T0, **kw)
+            r = h.route()
+            monkeypatch.delenv("FEMHEAT_RESIDENT_LAUNCH_MS")
+        assert (r["resident_launches"], r["resident_steps"]) == (7, 7)
+        same_bits(each, one)
+    monkeypatch.setenv("FEMHEAT_RESIDENT_LAUNCH_MS", "0")
+    st, res = fh.run_batch([p, p.replace(nsteps=2)], **opts)
+    assert st == fh.FEM_OK and fh.batch_route()["resident_steps"] == 9 and fh.batch_route()["resident_launches"] == 9  # in turn
+    monkeypatch.delenv("FEMHEAT_RESIDENT_LAUNCH_MS")
+    _, whole = fh.run_batch([p, p.replace(nsteps=2)], **opts)
+    for a, b in zip(res, whole):
+        same_bits(a, b)
+
+
+def stiff(n, nsteps):
+    """Steps that never converge: every one takes max_iter iterations."""
+    return wl.lognormal_cube(n, seed=3, nsteps=nsteps).replace(rtol=1e-30)
+
+
+def test_a_long_run_gives_the_device_back_in_between(gpu):
+    """128 steps of 300 iterations (about 2 ms each) are more than one launch
+    holds the device for (100 ms)."""
+    p = stiff(64, 128)
+    with fh.Heat.from_problem(p, max_iter=300) as h:
+        out = h.run(p.T0, dt=p.dt, theta=p.theta, nsteps=p.nsteps, rtol=p.rtol, check=False)
+        r = h.route()
+    say(f"  {out['device_ms']:.0f} ms in {r['resident_launches']} launches")
+    assert out["status"] == fh.FEM_ENOCONV and r["resident_steps"] == 128
+    assert max(2, out["device_ms"] / 110) <= r["resident_launches"] <= out["device_ms"] / 100 + 1
+
+
+def test_a_stiff_request_gives_the_device_back_after_each_step(gpu):
+    """Steps of 2 ms and more are as long as a server's launch may be: one per
+    epoch, so that requests of other sizes get their turn in between."""
+    p = stiff(80, 8)
+    with fh.Server(max_iter=400) as s:
+        st, _, _ = s.wait(s.submit(p))
+        assert st == fh.FEM_ENOCONV
+        assert s.info()["epochs"] == 8  # (two of four steps each without the bound)
