@@ -102,7 +102,8 @@ extern "C" {
                                blocks all fit the device at once (else two kernels).  The barrier
                                needs all of them resident: work that other streams or processes run
                                on the device at the same time can hold CUs, and then its bounded wait
-                               runs out and the run fails with FEM_EDEVICE.  Results agree with the
+                               runs out and the run fails with FEM_EDEVICE (resident launches of the
+                               same process, see fem_heat_run, take turns with it).  Results agree with the
                                two-kernel form to rounding (the r^T P^-1 r partials are summed per
                                gather block).  Batches and servers always use two kernels, so a
                                simulation's results do not depend on its co-runners */

@@ -262,10 +262,13 @@ class Engine {
 
   SimDev* sd_dev_ = nullptr;
   SimDev sd_one_{};  // host copy of the uploaded SimDev when the batch holds one simulation
-  // one-kernel iterations (FEM_ONE_KERNEL, runs of one handle); the grid-wide
+  // one-kernel iterations (FEM_ONE_KERNEL, runs of one handle): the compute
+  // units of a chunk of them, taken like a resident launch's (their blocks wait
+  // for each other too, and a resident launch may last 100 ms); the grid-wide
   // barrier's arrival counter followed by one flag per block (bar_blocks_ of
   // them), its failure flag, and the arrivals so far
   bool dirupd_ = false;
+  std::unique_ptr<ResidentGate> bar_gate_;
   unsigned long long* bar_count_ = nullptr;
   uint32_t bar_blocks_ = 0;
   // the failure flag in mapped pinned host memory: the host reads it after
@@ -752,6 +755,7 @@ int Engine::dirupd(BatchArgs a, hipEvent_t e0, hipEvent_t e1, bool* done) {
     u = UpdHalf<V>{s.r32, s.e32[a.xpar], s.iS[a.cur], s.iP[a.cur]};
     pinv = s.pinv32;
   }
+  if (!bar_gate_) bar_gate_ = std::make_unique<ResidentGate>(h->opts.device, h->cus, h->cus);
   bar_total_ += g.nwork;
   GridBar gb{bar_count_, bar_count_ + kBarFlagStride, bar_fail_, bar_total_, bar_spin_};
   uint32_t lb = lds_base;
@@ -762,7 +766,8 @@ int Engine::dirupd(BatchArgs a, hipEvent_t e0, hipEvent_t e1, bool* done) {
   // grid was checked against the device's occupancy above; work that other
   // streams or processes run at the same time can still hold CUs, and then
   // the barrier's bounded wait runs out and the run fails (FEM_ONE_KERNEL
-  // is an option for that reason).
+  // is an option for that reason).  Other kernels of this process whose blocks
+  // wait for each other are kept out by the gate.
   HIP_TRY(hipLaunchKernel(fn, dim3(g.nwork), dim3(g.nthreads), kargs, (unsigned int)smem, stream_));
   if (e1) HIP_TRY(hipEventRecord(e1, stream_));
   *done = true;
@@ -1030,6 +1035,7 @@ int Engine::pcg(int first_chunk) {
     const bool launch_next =
         !inner && !mixed_ && !cheb_ && act_.size() == 1 && act_[0]->step + 1 < act_[0]->rq.nsteps;
     RC_TRY(decide(inner, j + k, launch_next));
+    bar_gate_.reset();
     if (dirupd_) RC_TRY(check_barrier());  // a failed barrier left this chunk's results void
     bool all_done = true;
     int most = j;
@@ -1567,6 +1573,7 @@ int Engine::step(int* active, const ResBounds& bounds) {
 int Engine::run() {
   fem_heat* h = h_;
   for (auto& e : ev_run_) HIP_TRY(hipEventCreate(&e));
+  if (dirupd_) HIP_TRY(hipStreamSynchronize(stream_));  // a caller's earlier work ends outside the gate
   HIP_TRY(hipEventRecord(ev_run_[0], stream_));
   for (;;) {
     int active = 0;

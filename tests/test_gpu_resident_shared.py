@@ -1,6 +1,7 @@
 """Resident launches on a device that they do not have to themselves: blocks
 that wait for compute units, and work that waits for theirs."""
 import ctypes
+import threading
 import time
 
 import numpy as np
@@ -115,3 +116,36 @@ def test_a_stiff_request_gives_the_device_back_after_each_step(gpu):
         st, _, _ = s.wait(s.submit(p))
         assert st == fh.FEM_ENOCONV
         assert s.info()["epochs"] == 8  # (two of four steps each without the bound)
+
+
+def test_one_kernel_iterations_beside_resident_runs(gpu, monkeypatch):
+    """Runs with FEM_ONE_KERNEL while other threads' resident launches take
+    nearly every compute unit for 100 ms at a time: the grid barrier, whose
+    wait is made short (about 10 ms), never waits for them."""
+    busy = stiff(96, 40)
+    p = wl.lognormal_cube(48, seed=6, nsteps=20)
+    stop = threading.Event()
+    statuses = []
+
+    def keep_busy():
+        with fh.Heat.from_problem(busy, max_iter=400) as h:
+            while not stop.is_set():
+                statuses.append(h.run(busy.T0, dt=busy.dt, theta=busy.theta, nsteps=busy.nsteps, rtol=busy.rtol,
+                                      check=False)["status"])
+
+    with fh.Heat.from_problem(p, one_kernel=True, timing=True) as h:
+        kw = dict(dt=p.dt, theta=p.theta, nsteps=p.nsteps, rtol=p.rtol)
+        alone = h.run(p.T0, **kw)
+        assert h.stats()["one_kernel_launches"] > 0
+        monkeypatch.setenv("FEMHEAT_BARRIER_SPIN_LIMIT", "20000")
+        t = threading.Thread(target=keep_busy)
+        t.start()
+        try:
+            time.sleep(0.3)
+            beside = [h.run(p.T0, **kw) for _ in range(3)]
+        finally:
+            stop.set()
+            t.join()
+    assert set(statuses) == {fh.FEM_ENOCONV}
+    for out in beside:
+        same_bits(out, alone)
