@@ -106,7 +106,9 @@ hipError_t resident_launch(ResForm form, int kind, int planes, uint32_t blocks, 
                    : form == RES_CHEB ? resident_kernel_cheb(kind, planes)
                                       : resident_kernel_f64(kind, planes);
   if (!fn) return hipErrorInvalidValue;
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  // the same limit in every call: it is the kernel's, and another thread may be
+  // about to launch the kernel with more LDS than this launch takes
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLds);
   if (e != hipSuccess) return e;
   void* args[] = {&sims, &table};
   return hipLaunchKernel(fn, dim3(blocks), dim3((uint32_t)nthreads), args, lds, stream);
