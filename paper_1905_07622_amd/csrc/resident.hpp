@@ -584,12 +584,19 @@ struct ResClock {
 };
 
 // Puts the marker into the exchange vectors of every simulation of a launch
-// and clears its slots and words (blockIdx.y: simulation); the launch's own
-// words count from here.
-[[maybe_unused]] static __global__ void __launch_bounds__(256) resident_reset_kernel(const ResSim* sims, int mixed) {
-  const ResSim& S = sims[blockIdx.y];
-  const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, n = gridDim.x * blockDim.x, N = S.g.N;
-  if (S.s.nblk > 1) {
+// and clears its slots and words; the launch's own words count from here.
+[[maybe_unused]] static __global__ void __launch_bounds__(256) resident_reset_kernel(const ResSim* sims, uint32_t nsims,
+                                                                                    int mixed) {
+  const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, n = gridDim.x * blockDim.x;
+  if (blockIdx.y == 0 && tid == 0) {
+    gst(sims->launch, 0u, 0ull);
+    gst(sims->launch, 1u, (unsigned long long)wall_clock64());
+  }
+  for (uint32_t k = blockIdx.y; k < nsims; k += gridDim.y) {
+    const ResSim& S = sims[k];
+    const uint32_t N = S.g.N;
+    if (tid < 2) gst(S.ctl, tid, 0ull);
+    if (S.s.nblk == 1) continue;
     for (uint32_t i = tid; i < N; i += n) {
       if (mixed) {
         for (void* E : S.E) gst(static_cast<unsigned int*>(E), i, ResWord<float>::kEmpty);
@@ -602,11 +609,6 @@ struct ResClock {
       }
     }
     for (uint32_t i = tid; i < 2u * kResRep * S.s.nblk * 2u; i += n) gst(S.slots, i, 0ull);
-  }
-  if (tid < 2) gst(S.ctl, tid, 0ull);
-  if (blockIdx.y == 0 && tid == 0) {
-    gst(S.launch, 0u, 0ull);
-    gst(S.launch, 1u, (unsigned long long)wall_clock64());
   }
 }
 

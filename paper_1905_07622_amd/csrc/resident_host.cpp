@@ -114,6 +114,15 @@ hipError_t resident_launch(ResForm form, int kind, int planes, uint32_t blocks, 
   return hipLaunchKernel(fn, dim3(blocks), dim3((uint32_t)nthreads), args, lds, stream);
 }
 
+// Blocks over the nodes of a simulation (x), and simulations (y): the kernel
+// takes those past the grid in further rounds, as a batch may hold more than a
+// grid has rows (65535).
+dim3 resident_reset_grid(uint32_t n, uint32_t max_nodes) {
+  const uint32_t y = std::min<uint32_t>(std::max<uint32_t>(n, 1), 1024);
+  const uint32_t x = std::min<uint32_t>((max_nodes + 255) / 256, std::max<uint32_t>(8, 2048 / y));
+  return dim3(std::max<uint32_t>(1, x), y);
+}
+
 ResidentGate::ResidentGate(int device, int cus, int want) : device_(device), want_(std::min(want, cus)) {
   GateState& s = gates()[(size_t)device];
   std::unique_lock<std::mutex> lk(s.mu);

@@ -15,7 +15,9 @@ ResShape resident_shape(const Geom& g, const fem_opts& o, bool batched, int cus)
 // and the same planes per brick.
 hipError_t resident_launch(ResForm form, int kind, int planes, uint32_t blocks, int nthreads, size_t lds,
                            hipStream_t stream, const ResSim* sims, const uint2* table);
+// Prepares the launches of a pass: n simulations of at most max_nodes nodes.
 hipError_t resident_reset(hipStream_t stream, const ResSim* sims, uint32_t n, ResForm form, uint32_t max_nodes);
+dim3 resident_reset_grid(uint32_t n, uint32_t max_nodes);
 
 // Compute units of one device, taken by resident launches of this process:
 // two kernels whose blocks wait for blocks of their own must both fit, or

@@ -149,3 +149,17 @@ def test_one_kernel_iterations_beside_resident_runs(gpu, monkeypatch):
     assert set(statuses) == {fh.FEM_ENOCONV}
     for out in beside:
         same_bits(out, alone)
+
+
+@pytest.mark.parametrize("opts", [{}, dict(precision=fh.FEM_FP32_FP64DOT)])
+def test_more_simulations_than_the_preparing_grid_has_rows(gpu, opts):
+    """1100 small simulations of several bricks in one launch (the kernel that
+    prepares a launch takes 1024 at a time): each bit for bit as alone."""
+    probs = [wl.random_problem(1, 1, 39, seed=s % 50, nsteps=2, rtol=1e-9) for s in range(1100)]
+    st, res = fh.run_batch(probs, **opts)
+    r = fh.batch_route()
+    assert st == fh.FEM_OK and (r["resident_steps"], r["unmet"]) == (2200, 0)
+    for s in range(50):
+        _, alone = fh.run_batch([probs[s]], **opts)
+        for k in range(s, 1100, 50):
+            same_bits(res[k], alone[0])

@@ -65,3 +65,17 @@ int main() {
   return 0;
 }
 """)
+
+
+@pytest.mark.parametrize("n", [1, 2, 64, 1023, 1024, 1025, 65535, 65536, 1000000])
+def test_reset_grid_fits_any_number_of_simulations(tmp_path, n):
+    run(tmp_path, f"""
+int main() {{
+  for (uint32_t nodes : {{8u, 257u, 1u << 20}}) {{
+    const dim3 g = resident_reset_grid({n}u, nodes);
+    CHECK(g.x >= 1 && g.y >= 1 && g.z == 1 && g.y <= 65535u && (uint64_t)g.x * g.y <= 16384);
+    CHECK({n}u > 65535u || g.y == std::min({n}u, 1024u));
+  }}
+  return 0;
+}}
+""")
