@@ -23,6 +23,12 @@ using femheat::CoefficientArrays;
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
+// Nodes of a grid with at least one element per axis (2^31 - 1 elements along
+// one are in range, their nodes are not).
+double node_count(const fem_grid& g) { return ((double)g.nx + 1.0) * ((double)g.ny + 1.0) * ((double)g.nz + 1.0); }
+// kernels address FP64 node vectors with 32-bit byte offsets
+constexpr double kMaxNodes = 536870912.0;
+
 // Reads n doubles from host or device memory for validation.
 bool fetch(const double* src, size_t n, bool device, std::vector<double>& out) {
   out.resize(n);
@@ -87,9 +93,7 @@ int check_problem(const fem_grid* grid, const double* k_e, const double* rhoc_e,
   };
   if (!grid || !k_e || !rhoc_e) return bad("grid, k_e and rhoc_e are required");
   if (grid->nx < 1 || grid->ny < 1 || grid->nz < 1) return bad("nx, ny, nz must be >= 1");
-  const double N = (double)(grid->nx + 1) * (grid->ny + 1) * (grid->nz + 1);
-  // kernels address FP64 node vectors with 32-bit byte offsets
-  if (N >= 536870912.0) return bad("grid too large (N must be below 2^29 nodes)");
+  if (node_count(*grid) >= kMaxNodes) return bad("grid too large (N must be below 2^29 nodes)");
   if (!finite_pos(grid->hx) || !finite_pos(grid->hy) || !finite_pos(grid->hz)) return bad("h must be finite and > 0");
   if (o.element == FEM_ELEM_TET6 && !(grid->hx == grid->hy && grid->hy == grid->hz))
     return bad("the tetrahedral element needs cubic boxes (hx = hy = hz)");
@@ -249,7 +253,7 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
     for (int32_t i = 0; i < n && plain; ++i) {
       const fem_grid& g = reqs[i].grid;
       plain = g.nx >= 1 && g.ny >= 1 && g.nz >= 1 && reqs[i].k_e && reqs[i].rhoc_e &&
-              (double)(g.nx + 1) * (g.ny + 1) * (g.nz + 1) < 536870912.0;
+              node_count(g) < kMaxNodes;
       if (plain) arrays.push_back({reqs[i].k_e, reqs[i].rhoc_e, (size_t)g.nx * g.ny * g.nz});
     }
     flags.assign((size_t)n, 0);
