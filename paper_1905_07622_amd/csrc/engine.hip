@@ -1364,9 +1364,8 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
   });
   const size_t n = act.size();
   std::vector<int> steps(n);
-  std::vector<size_t> slot(n);
   std::vector<char> first(n, 0);  // of its launch
-  size_t nsteps = 0, nblocks = 0, nslots = 2;  // (the first words: the launches' own)
+  size_t nsteps = 0, nblocks = 0;
   uint32_t max_nodes = 0;
   for (size_t k = 0; k < n; ++k) {
     const Sim& s = *act[k];
@@ -1389,27 +1388,25 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
     l.blocks += sh->res.nblk;
     nblocks += sh->res.nblk;
     nsteps += (size_t)m;
-    slot[k] = nslots;
-    nslots += (size_t)2 * kResRep * sh->res.nblk * 2 + 2 + (size_t)sh->res.nblk * sh->res.nthreads * kResHalo;
     max_nodes = std::max(max_nodes, sh->g.N);
   }
   // one buffer: records, block table, load factors and results (uploaded), step
-  // records (with the results, downloaded), slots and stash (on the device only)
+  // records (with the results, downloaded), the launch's words (on the device only)
   auto up = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t o_tab = up(n * sizeof(ResSim)), o_fs = o_tab + up(nblocks * sizeof(uint2)),
                o_out = o_fs + up(nsteps * sizeof(double)), o_rec = o_out + up(n * sizeof(ResOut)),
-               o_slot = o_rec + up(nsteps * sizeof(ResStep)), bytes = o_slot + up(nslots * 8);
+               o_words = o_rec + up(nsteps * sizeof(ResStep)), bytes = o_words + 2 * sizeof(unsigned long long);
   // a single run keeps its buffers with the handle
   ResStage& st = keep_stage_ ? act[0]->rq.h->res_stage : own_stage_;
-  if (st.cap < bytes || st.host_cap < o_slot) {
+  if (st.cap < bytes || st.host_cap < o_words) {
     HIP_TRY(hipStreamSynchronize(stream_));
     efree(st.dev);
     if (st.host) (void)hipHostFree(st.host);
     st = ResStage{};
     RC_TRY(ealloc(&st.dev, bytes));
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&st.host), o_slot, hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&st.host), o_words, hipHostMallocDefault));
     st.cap = bytes;
-    st.host_cap = o_slot;
+    st.host_cap = o_words;
   }
   ResSim* sims = reinterpret_cast<ResSim*>(st.host);
   uint2* tab = reinterpret_cast<uint2*>(st.host + o_tab);
@@ -1484,11 +1481,10 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
     r.T[0] = s.T1;
     r.T[1] = s.T2;
     r.T[2] = s.X[0];
-    unsigned long long* words = reinterpret_cast<unsigned long long*>(st.dev + o_slot) + slot[k];
-    r.ctl = words;
-    r.launch = reinterpret_cast<unsigned long long*>(st.dev + o_slot);
-    r.slots = words + 2;
-    r.stash = r.slots + (size_t)2 * kResRep * sh->res.nblk * 2;
+    r.launch = reinterpret_cast<unsigned long long*>(st.dev + o_words);
+    r.ctl = sh->res_words;
+    r.slots = r.ctl + 2;
+    r.stash = r.slots + res_slot_words(sh->res);
     r.fs = reinterpret_cast<const double*>(st.dev + o_fs) + at;
     r.rec = reinterpret_cast<ResStep*>(st.dev + o_rec) + at;
     r.out = reinterpret_cast<ResOut*>(st.dev + o_out) + k;
@@ -1532,7 +1528,7 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
                               reinterpret_cast<const ResSim*>(st.dev),
                               n == 1 ? nullptr : reinterpret_cast<const uint2*>(st.dev + o_tab) + l.off));
     route.resident_launches += (int64_t)launches.size();
-    HIP_TRY(hipMemcpyAsync(st.host + o_out, st.dev + o_out, o_slot - o_out, hipMemcpyDeviceToHost, stream_));
+    HIP_TRY(hipMemcpyAsync(st.host + o_out, st.dev + o_out, o_words - o_out, hipMemcpyDeviceToHost, stream_));
     HIP_TRY(hipStreamSynchronize(stream_));
   }
   ++passes_;

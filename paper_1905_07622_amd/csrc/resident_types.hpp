@@ -96,6 +96,13 @@ struct ResSim {
   uint64_t hold;              // device clock ticks that the launch lasts at most
 };
 
+// 8-byte words of a simulation's own scratch: the control words, the slots of
+// the sums, the stash.
+__host__ __device__ constexpr size_t res_slot_words(const ResShape& s) { return (size_t)2 * kResRep * s.nblk * 2; }
+__host__ __device__ constexpr size_t res_words(const ResShape& s) {
+  return 2 + res_slot_words(s) + (size_t)s.nblk * (size_t)s.nthreads * kResHalo;
+}
+
 // Values of a brick's node array: its columns with the halo, and one column
 // that takes the writes of lanes without a node; a multiple of 4 (alignment).
 __host__ __device__ constexpr int res_nodes(int a, int b, int c) { return (((a + 2) * (b + 2) + 1) * (c + 2) + 3) / 4 * 4; }

@@ -514,6 +514,7 @@ int solver_init(fem_heat* h, const fem_grid* grid, const double* k_e, const doub
   for (auto& p : h->pool) RC_TRY(dalloc(h, &p, N));
   if (h->nonzero_dirichlet) RC_TRY(dalloc(h, &h->lift64, N));
   RC_TRY(dalloc(h, &h->sink, kMaxBlockThreads));
+  if (h->res.nblk > 0) RC_TRY(dalloc(h, &h->res_words, res_words(h->res)));
   h->n_partials = std::max({h->shape.nblocks, h->upd_blocks64, h->upd_blocks32, h->start_blocks});
   const size_t ncomp = one_red ? 4 : 1;  // the one-reduction direction kernel publishes four sums per block
   for (RelayCtx* c : {&h->outer, &h->inner})
@@ -761,6 +762,18 @@ size_t handle_device_bytes(const fem_grid& grid, const fem_opts& opts, const fem
   // relay state and partials (at most max(tiles, update blocks) per buffer) and the sink
   const size_t tiles_bound = N / 32 + 1024;
   bytes += 4 * (sizeof(Scalars) + 8 * tiles_bound * (one_red ? 4 : 1)) + 8 * kMaxBlockThreads;
+  // the resident form's scratch (a server's simulations take a batch member's cut)
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, opts.device) != hipSuccess) {
+    (void)hipGetLastError();
+    cus = kResBlocks;
+  }
+  Geom g{};
+  g.px = grid.nx + 1;
+  g.py = grid.ny + 1;
+  g.pz = grid.nz + 1;
+  const ResShape cut = resident_shape(g, opts, true, cus);
+  if (cut.nblk > 0) bytes += 8 * res_words(cut);
   if (n_sensors > 0) bytes += 8 * (3 * (size_t)n_sensors + (size_t)std::max(nsteps, 1) * n_sensors);
   return bytes;
 }
@@ -801,6 +814,7 @@ void solver_free(fem_heat* h) {
   dfree(h, h->xyz_dev);
   dfree(h, h->traces_dev);
   dfree(h, h->ebe_part);
+  dfree(h, h->res_words);
   dfree(h, h->res_stage.dev);
   if (h->res_stage.host) (void)hipHostFree(h->res_stage.host);
   h->res_stage = ResStage{};

@@ -25,7 +25,7 @@ struct ResShape {
   int32_t nthreads;
 };
 
-// Buffers of a resident launch: the records and results, pinned and on the device.
+// Buffers of a resident launch: its words, records and results, pinned and on the device.
 struct ResStage {
   unsigned char* host = nullptr;
   unsigned char* dev = nullptr;
@@ -102,8 +102,10 @@ struct fem_heat {
   bool tuned = false;     // the shape came from the autotuner's cache
   uint32_t upd_blocks64 = 0, upd_blocks32 = 0, start_blocks = 0;
 
-  // resident form: the cut (nblk = 0: two kernels) and a single run's buffers
+  // resident form: the cut (nblk = 0: two kernels), the scratch of its blocks
+  // (res_words) and a single run's buffers
   femheat::ResShape res{};
+  unsigned long long* res_words = nullptr;
   femheat::ResStage res_stage;
   int32_t cus = 1;
 
