@@ -1398,15 +1398,16 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
                o_words = o_rec + up(nsteps * sizeof(ResStep)), bytes = o_words + 2 * sizeof(unsigned long long);
   // a single run keeps its buffers with the handle
   ResStage& st = keep_stage_ ? act[0]->rq.h->res_stage : own_stage_;
-  if (st.cap < bytes || st.host_cap < o_words) {
+  if (st.cap < bytes) {
     HIP_TRY(hipStreamSynchronize(stream_));
     efree(st.dev);
     if (st.host) (void)hipHostFree(st.host);
+    // (grows geometrically, as the other tables do: see compose)
+    const size_t cap = std::max<size_t>({bytes, 2 * st.cap, 16384});
     st = ResStage{};
-    RC_TRY(ealloc(&st.dev, bytes));
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&st.host), o_words, hipHostMallocDefault));
-    st.cap = bytes;
-    st.host_cap = o_words;
+    RC_TRY(ealloc(&st.dev, cap));
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&st.host), cap, hipHostMallocDefault));
+    st.cap = cap;
   }
   ResSim* sims = reinterpret_cast<ResSim*>(st.host);
   uint2* tab = reinterpret_cast<uint2*>(st.host + o_tab);
@@ -1483,7 +1484,7 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
     r.T[2] = s.X[0];
     r.launch = reinterpret_cast<unsigned long long*>(st.dev + o_words);
     r.ctl = sh->res_words;
-    r.slots = r.ctl + 2;
+    r.slots = r.ctl + kResCtl;
     r.stash = r.slots + res_slot_words(sh->res);
     r.fs = reinterpret_cast<const double*>(st.dev + o_fs) + at;
     r.rec = reinterpret_cast<ResStep*>(st.dev + o_rec) + at;

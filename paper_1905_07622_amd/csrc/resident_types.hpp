@@ -96,11 +96,12 @@ struct ResSim {
   uint64_t hold;              // device clock ticks that the launch lasts at most
 };
 
-// 8-byte words of a simulation's own scratch: the control words, the slots of
-// the sums, the stash.
+// 8-byte words of a simulation's own scratch: the control words (in a cache
+// line of their own), the slots of the sums, the stash.
+constexpr size_t kResCtl = 16;
 __host__ __device__ constexpr size_t res_slot_words(const ResShape& s) { return (size_t)2 * kResRep * s.nblk * 2; }
 __host__ __device__ constexpr size_t res_words(const ResShape& s) {
-  return 2 + res_slot_words(s) + (size_t)s.nblk * (size_t)s.nthreads * kResHalo;
+  return kResCtl + res_slot_words(s) + (size_t)s.nblk * (size_t)s.nthreads * kResHalo;
 }
 
 // Values of a brick's node array: its columns with the halo, and one column

@@ -29,7 +29,7 @@ struct ResShape {
 struct ResStage {
   unsigned char* host = nullptr;
   unsigned char* dev = nullptr;
-  size_t cap = 0, host_cap = 0;
+  size_t cap = 0;  // of either
 };
 }  // namespace femheat
 

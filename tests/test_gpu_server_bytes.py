@@ -3,6 +3,7 @@ takes on the device, counted by a caller's allocator."""
 import ctypes
 import threading
 
+import numpy as np
 import pytest
 
 from paper_1905_07622_amd import femheat as fh
@@ -24,7 +25,7 @@ class Counting:
     """hipMalloc / hipFree, with the bytes held and their peak."""
 
     def __init__(self):
-        self.size, self.held, self.peak, self.mu = {}, 0, 0, threading.Lock()
+        self.size, self.held, self.peak, self.calls, self.mu = {}, 0, 0, 0, threading.Lock()
         hip = fh.lib()
         hip.hipFree.argtypes = [ctypes.c_void_p]
 
@@ -34,6 +35,7 @@ class Counting:
             with self.mu:
                 self.size[ptr[0]] = n
                 self.held += n
+                self.calls += 1
                 self.peak = max(self.peak, self.held)
             return 0
 
@@ -70,3 +72,23 @@ def test_charged_bytes_cover_the_device_memory(gpu, dims, opts):
     # the lane's own records are not a request's: 8 KiB and 16 bytes a brick or block each
     assert c.peak <= info["peak_bytes_in_use"] + 3 * 64 * 1024
     assert c.held == 0
+
+
+def test_a_launchs_buffers_grow_geometrically(gpu):
+    """Runs of 1, 2, ... 300 steps on one handle: the records of a launch grow
+    with the steps, but their buffers (pinned, on the device: replacing them
+    waits for every stream) are replaced a few times only."""
+    p = wl.random_problem(4, 4, 4, seed=2, nsteps=1, rtol=1e-6)
+    c = Counting()
+    opts = fh.make_opts()
+    opts.allocator = ctypes.addressof(c.struct)
+    k, r, T = (np.ascontiguousarray(a).ctypes.data_as(fh._dp) for a in (p.k_e, p.rhoc_e, p.T0))
+    st, h = fh.fem_heat_create(fh.fem_grid(p.nx, p.ny, p.nz, p.hx, p.hy, p.hz), k, r, None, opts)
+    assert st == fh.FEM_OK
+    made = c.calls
+    for nsteps in range(1, 301):
+        assert fh.fem_heat_run(h, T, None, p.dt, p.theta, nsteps, p.rtol, None) == fh.FEM_OK
+    grown = c.calls - made
+    fh.fem_heat_destroy(h)
+    say(f"  {grown} allocations in 300 runs")
+    assert grown <= 4 and c.held == 0
