@@ -197,7 +197,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // The value v, opaque to the compiler: addresses formed from it are formed
-// where they are used.  (Hoisted out of the kernel's one loop, the addresses
+// where they are used.  (Hoisted out of the kernel's loops, the addresses
 // of all its phases would take the registers that the brick's vectors need.)
 __device__ __forceinline__ int here(int v) {
   asm volatile("" : "+v"(v));
@@ -308,9 +308,9 @@ __device__ inline void brick_setup(Brick& B, const Geom& g, const ResShape& s, u
 
 // The operator at the nodes of the thread's column: acc[z] for plane z of
 // the brick, from the input in D (planes 0 .. L+1) and the coefficients in C
-// (layers 0 .. L).  Straight-line code.  The next plane (kAhead: and the next
-// layer's coefficients) is read while a layer is summed.
-template <typename V, int KIND, int L, bool kAhead>
+// (layers 0 .. L).  Straight-line code.  The next plane and the next layer's
+// coefficients are read while a layer is summed.
+template <typename V, int KIND, int L>
 __device__ __forceinline__ void brick_apply(const Brick& B, const V* D, const V* C, const V* Mc, const V* Kc,
                                             V (&acc)[L]) {
   constexpr int P = kResPitch<L>;
@@ -344,17 +344,16 @@ __device__ __forceinline__ void brick_apply(const Brick& B, const V* D, const V*
   Coefs cc, cn;
   plane(std::integral_constant<int, 0>{}, lo);
   plane(std::integral_constant<int, 1>{}, hi);
-  if constexpr (kAhead) coefs(std::integral_constant<int, 0>{}, cc);
+  coefs(std::integral_constant<int, 0>{}, cc);
   V carry = V(0);
   each<L + 1>([&](auto k) FEM_INLINE {
     // one layer at a time: the compiler would otherwise read the whole column
     // into registers first, which the brick's vectors need, and form the sums
     // where they are used
-    if constexpr (k < L) plane(std::integral_constant<int, k + 2>{}, next);
-    if constexpr (!kAhead)
-      coefs(k, cc);
-    else if constexpr (k < L)
+    if constexpr (k < L) {
+      plane(std::integral_constant<int, k + 2>{}, next);
       coefs(std::integral_constant<int, k + 1>{}, cn);
+    }
     __builtin_amdgcn_sched_barrier(0);
     V p_lo, p_hi;
     auto coef = [&](int sx, int sy, V& a, V& bk) FEM_INLINE {
@@ -366,7 +365,7 @@ __device__ __forceinline__ void brick_apply(const Brick& B, const V* D, const V*
     carry = p_hi;
     lo = hi;
     hi = next;
-    if constexpr (kAhead) cc = cn;
+    cc = cn;
     if constexpr (k > 0) asm volatile("" : "+v"(acc[k - 1]), "+v"(carry)::"memory");
     __builtin_amdgcn_sched_barrier(0);
   });
@@ -621,7 +620,6 @@ template <typename V, int KIND, int L, bool CHEB>
 __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __restrict__ sims,
                                                                const uint2* __restrict__ table) {
   constexpr bool kMixed = sizeof(V) == 4;
-  constexpr bool kAhead = true;
   extern __shared__ __align__(16) unsigned char res_smem[];
   __shared__ int lost, go;
   __shared__ ResClock clk;
@@ -709,7 +707,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(const ResSim* __r
         Kc[c] = k[c];
       }
     }
-    brick_apply<W, KIND, L, kAhead>(B, at, coefs, Mc, Kc, acc);
+    brick_apply<W, KIND, L>(B, at, coefs, Mc, Kc, acc);
   };
   using U = typename ResWord<V>::U;
   using U64 = ResWord<double>::U;

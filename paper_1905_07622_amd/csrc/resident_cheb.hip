@@ -1,5 +1,5 @@
 // Resident kernels of the FP64 form with the Chebyshev preconditioner (see
-// resident.hpp) for every element kind and brick height; one file per form,
+// resident.hpp) for hexahedra and every brick height; one file per form,
 // so that they build side by side.
 #include "resident_kernels.hpp"
 

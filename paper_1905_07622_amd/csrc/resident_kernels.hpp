@@ -17,9 +17,14 @@ const void* resident_kernel_planes(int planes) {
 
 template <typename V, bool CHEB>
 const void* resident_kernel_of(int kind, int planes) {
-  return kind == kElemCubic  ? resident_kernel_planes<V, kElemCubic, CHEB>(planes)
-         : kind == kElemTet6 ? resident_kernel_planes<V, kElemTet6, CHEB>(planes)
-                             : resident_kernel_planes<V, kElemBox, CHEB>(planes);
+  if (kind == kElemCubic) return resident_kernel_planes<V, kElemCubic, CHEB>(planes);
+  if (kind == kElemTet6) {
+    if constexpr (CHEB)  // (tetrahedra run with the Jacobi preconditioner)
+      return nullptr;
+    else
+      return resident_kernel_planes<V, kElemTet6, CHEB>(planes);
+  }
+  return resident_kernel_planes<V, kElemBox, CHEB>(planes);
 }
 
 }  // namespace femheat
