@@ -9,7 +9,7 @@ N * (PCG iterations) / wall time / 1e6 over the timed steps, FP64.
 Printed as one JSON line with a roofline object for the dominant kernel
 (algorithmic bytes per launch / average launch time measured with HIP events
 over the timed region; in the resident form, operations per iteration /
-sampled iteration time) and a CPU baseline (the oracle on a bounded sample).
+time per iteration of the run) and a CPU baseline (the oracle on a bounded sample).
 The same line carries the batched-proposals result ("batched": 64 x 48^3
 simulations in one fem_heat_run_batch call) and the serving result
 ("served": a Poisson request stream through fem_server), each next to the
@@ -69,12 +69,20 @@ VECTOR_PEAK_TFLOPS = {8: 78.6, 4: 157.3}
 RESIDENT_FLOPS = 4 * 27 + 7 + 11
 
 
-def resident_roofline(N: int, w: int, per_ms: dict) -> dict:
+def form_taken(route: dict, otherwise: str = "two-kernel") -> str:
+    """The form that took a run's steps, from the library's own count (fem_heat_route)."""
+    if route["resident_steps"] == 0:
+        return otherwise
+    return "resident" if route["two_kernel_steps"] == 0 else f"resident, then {otherwise}"
+
+
+def resident_roofline(N: int, w: int, us: float, per_ms: dict) -> dict:
     """Roofline of the resident form, whose vectors stay on chip from step to
-    step (no bytes to count per iteration): operations of an iteration /
-    sampled time of its two halves, against the vector rate.  What bounds it is
-    latency: two sums over all blocks and the march in between."""
-    us = sum(per_ms.values()) * 1e3
+    step (no bytes to count per iteration): operations of an iteration / its
+    share `us` of the run, against the vector rate.  What bounds it is latency:
+    two sums over all blocks and the march in between.  (The sampled halves,
+    march with d^T q and update with exchange, leave out the next direction and
+    what a step does outside its iterations.)"""
     achieved = RESIDENT_FLOPS * N / us / 1e6
     return {"bound": "fp64 vector" if w == 8 else "fp32 vector", "kernel": "resident", "achieved": round(achieved, 2),
             "peak": VECTOR_PEAK_TFLOPS[w], "unit": "TFLOP/s", "frac": round(achieved / VECTOR_PEAK_TFLOPS[w], 4),
@@ -192,14 +200,18 @@ def bench_mixed(args, torch, p, k, rc, T0, T_fp64):
                 stream=stream, one_kernel=args.pcg_form == "one-kernel",
                 tune_cache=getattr(args, "tune_cache_path", None))
     run_kw = dict(dt=p.dt, theta=p.theta, nsteps=p.nsteps, rtol=p.rtol)
-    tuned = h.tune(dt=p.dt, theta=p.theta) if getattr(args, "tune_cache_path", None) else None
+    h.run(T0, **dict(run_kw, nsteps=1))
+    tuned = None  # a resident run has no gather tile
+    if getattr(args, "tune_cache_path", None) and form_taken(h.route()) != "resident":
+        tuned = h.tune(dt=p.dt, theta=p.theta)
     rate, its, last = _timed_runs(h, T0, run_kw, 2)
+    form = form_taken(h.route(), args.pcg_form)
     h.close()
     diff = torch.linalg.vector_norm(last["T_final"] - T_fp64) / torch.linalg.vector_norm(T_fp64)
     print(f"mixed: {rate * p.n_nodes:.1f} MDOF*iter/s", file=sys.stderr, flush=True)
     return {"workload": "the headline workload in the mixed form", "value": round(rate * p.n_nodes, 1),
             "unit": "MDOF*iter/s", "iterations_per_run": int(its),
-            "sweeps_per_step_max": int(last["refine_sweeps"].max()), "autotuned": tuned,
+            "sweeps_per_step_max": int(last["refine_sweeps"].max()), "pcg_form": form, "autotuned": tuned,
             "rel_l2_vs_fp64_final_field": float(diff)}
 
 
@@ -219,7 +231,7 @@ def bench_above_mall(args, torch):
     run_kw = dict(dt=p.dt, theta=p.theta, nsteps=p.nsteps, rtol=p.rtol)
     t0 = time.perf_counter()
     rate, its, last = _timed_runs(h, T0, run_kw, 2)
-    form = "one-kernel" if h.stats()["one_kernel_launches"] > 0 else "two-kernel"
+    form = form_taken(h.route(), "one-kernel" if h.stats()["one_kernel_launches"] > 0 else "two-kernel")
     h.close()
     f_corr = deferred_fraction(last["iters"].cpu().numpy())
     ab = algorithmic_bytes(p.n_nodes, p.n_elems, 8, f_corr, form)
@@ -345,7 +357,9 @@ def bench_batched(args, torch):
     prec = fh.FEM_FP32_FP64DOT if args.batch_precision == "mixed" else fh.FEM_FP64
     cache = getattr(args, "tune_cache_path", None)
     tuned = None
-    if cache:  # batch-member tile for this grid, recorded in the cache the batched call reads
+    fh.run_batch([p.replace(nsteps=1) for p in probs[:2]], precision=prec, device_ptrs=True, stream=stream)
+    form = form_taken(fh.batch_route())
+    if cache and form != "resident":  # batch-member tile for this grid, recorded in the cache the batched call reads
         with fh.Heat.from_problem(probs[0], precision=prec, device_ptrs=True, stream=stream, tune_cache=cache) as th:
             tuned = th.tune(dt=probs[0].dt, theta=probs[0].theta, batch=True)
         print(f"batched: tuned batch-member tile {tuned}", file=sys.stderr, flush=True)
@@ -365,8 +379,10 @@ def bench_batched(args, torch):
            "solves_per_s": round(len(probs) / t_batch, 3), "seconds": round(t_batch, 3),
            "seconds_of_three_runs": [round(t, 3) for t in times],
            "nodes_per_sim": probs[0].n_nodes, "iterations_per_sim_mean": float(np.mean([r["total_iters"] for r in res])),
-           "autotuned_member_tile": tuned,
-           "concurrent_batches": max(1, min(3, len(probs) // 16, sum(p.n_nodes for p in probs) >> 21))}
+           "autotuned_member_tile": tuned, "pcg_form": form,
+           # (simulations in the two-kernel form are dealt to as many batches; resident ones share one launch)
+           "concurrent_batches": 1 if form == "resident" else
+           max(1, min(3, len(probs) // 16, sum(p.n_nodes for p in probs) >> 21))}
     plain = {}
     refs = {}
     for rtol in (1e-8,) + tuple(args.loose_rtols):
@@ -455,6 +471,9 @@ def bench_served(args, torch):
     if cache:  # batch-member tiles of every serving grid, recorded in the cache the servers read
         for edge in wl.SERVE_EDGES:
             q = next(r for r in reqs if r.nx == edge)
+            fh.run_batch([q.replace(nsteps=1)], precision=prec)
+            if form_taken(fh.batch_route()) == "resident":
+                continue
             with fh.Heat.from_problem(q, precision=prec, tune_cache=cache) as th:
                 th.tune(dt=q.dt, theta=q.theta, batch=True)
     _plain_solve(_to_device(reqs[0].replace(nsteps=3), torch), 1e-8, stream)  # warm-up
@@ -570,10 +589,11 @@ def bench_cheb(args, torch, p, k, rc, T0, jac_ms, jac_iters, T_jac):
         r = h.run(T0, **kw)
         torch.cuda.synchronize()
         ms = (time.perf_counter() - t0) * 1e3
+        form = form_taken(h.route())
         h.close()
         its = int(r["total_iters"])
         out[f"degree_{m}"] = {"ms_per_run": round(ms, 2), "iterations_per_run": its,
-                              "gathers_per_run": its * m, "speedup_vs_jacobi": round(jac_ms / ms, 3),
+                              "pcg_form": form, "gathers_per_run": its * m, "speedup_vs_jacobi": round(jac_ms / ms, 3),
                               "MDOF_iter_per_s": round(p.n_nodes * its / ms / 1e3, 1),
                               "rel_l2_vs_jacobi_field": _rel(r["T_final"], T_jac, torch)}
         print(f"chebyshev m={m}: {its} iterations, {ms:.1f} ms (Jacobi {jac_iters}, {jac_ms:.1f} ms)",
@@ -604,9 +624,10 @@ def bench_laminate(args, torch):
                 r = h.run(p.T0, **kw)
                 torch.cuda.synchronize()
                 secs = time.perf_counter() - t0
+                form = form_taken(h.route())
             its = int(r["total_iters"])
             row["dof"] = p.n_nodes
-            row[name] = {"iterations": its, "ms_total": round(secs * 1e3, 2),
+            row[name] = {"iterations": its, "pcg_form": form, "ms_total": round(secs * 1e3, 2),
                          "us_per_iteration": round(secs * 1e6 / max(its, 1), 2),
                          "MDOF_iter_per_s": round(p.n_nodes * its / secs / 1e6, 1)}
         row["paper_fg_dbd_iterations"] = paper_iters.get(n)
@@ -764,7 +785,8 @@ def main():
                 tune_cache=tune_cache)
     run_kw = dict(dt=p.dt, theta=p.theta, nsteps=p.nsteps, rtol=p.rtol)
     tuned = None
-    if tune_cache and args.tile == (0, 0, 0):
+    h.run(T0, **dict(run_kw, nsteps=1))
+    if tune_cache and args.tile == (0, 0, 0) and form_taken(h.route()) != "resident":
         # the autotuner times the hot gather's candidate tiles on this grid and installs the fastest
         tuned = h.tune(dt=p.dt, theta=p.theta)
         print(f"tuned tile {tuned}", file=sys.stderr, flush=True)
@@ -794,6 +816,7 @@ def main():
     secs = t1 - t0
     value = p.n_nodes * iters / secs / 1e6
     shape = h.stats()
+    route = h.route()  # of the last run
     h.close()
 
     w = 8 if args.precision == "fp64" else 4
@@ -802,20 +825,20 @@ def main():
     form = args.pcg_form
     if form == "one-kernel" and stats["one_kernel_launches"] == 0:
         form = "two-kernel"  # the launch could not hold every block at once
-    single = form != "two-kernel"
+    form = form_taken(route, form)
+    on_chip = form.startswith("resident")
+    single = form in ("one-kernel", "one-reduction")
     ab = algorithmic_bytes(p.n_nodes, p.n_elems, w, f_corr, form)
-    roof = None
+    roof = per = None
     if stats["gather_launches"] and (stats["update_launches"] or single):
         per = {"gather": stats["gather_ms"] / stats["gather_launches"]}
         if stats["update_launches"]:
             per["update"] = stats["update_ms"] / stats["update_launches"]
         dom = max(per, key=lambda kname: stats[kname + "_ms"])
         achieved = ab[dom] / (per[dom] * 1e-3) / 1e9
-        # a rate that the memory cannot deliver (at half the bytes, half of it): the vectors stayed on chip
-        if form == "two-kernel" and ab["gather"] / (per["gather"] * 1e-3) / 1e9 > HBM_PEAK_GBS * w / 8:
-            form = "resident"
-            roof = resident_roofline(p.n_nodes, w, per)
-    if roof is None and stats["gather_launches"] and (stats["update_launches"] or single):
+    if form == "resident" and per is not None:
+        roof = resident_roofline(p.n_nodes, w, secs * 1e6 / max(iters, 1), per)
+    elif not on_chip and per is not None:
         roof = {"bound": "hbm", "kernel": dom, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": committed_traffic(dom, args.precision, form),
@@ -828,7 +851,7 @@ def main():
                                           "bytes_per_launch": int(round(ab[kname]))}
                                   for kname, v in per.items() if kname != dom and ab.get(kname)}}
 
-    per_iter = algorithmic_bytes(p.n_nodes, p.n_elems, w, f_corr, "two-kernel" if form == "resident" else form)
+    per_iter = algorithmic_bytes(p.n_nodes, p.n_elems, w, f_corr, form)
     iter_bytes = per_iter["gather"] + per_iter["update"]
     runs = {"n": len(run_ms), "median_ms": round(float(np.median(run_ms)), 2),
             "min_ms": round(min(run_ms), 2), "max_ms": round(max(run_ms), 2),
@@ -883,8 +906,9 @@ def main():
                                f"{p.nsteps} steps, rtol 1e-8, Jacobi-PCG", "seed": 2,
                    "precision": args.precision, "pcg_form": form,
                    "iterations_per_run": int(last["total_iters"]),
-                   "tile": [shape["tile_x"], shape["tile_y"], shape["tile_z"]],
-                   "grid_blocks": shape["grid_blocks"], "autotuned": tuned},
+                   # of the gather's launches; a resident run has none
+                   "tile": None if form == "resident" else [shape["tile_x"], shape["tile_y"], shape["tile_z"]],
+                   "grid_blocks": None if form == "resident" else shape["grid_blocks"], "autotuned": tuned},
         "roofline": roof,
         "runs": runs,
     }
