@@ -168,78 +168,14 @@ int check_run(const femheat::Geom& g, bool dev, const double* T0, double dt, dou
   return FEM_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-void fem_heat_default_opts(fem_opts* o) {
-  if (!o) return;
-  std::memset(o, 0, sizeof(*o));
-  o->precision = FEM_FP64;
-  o->max_iter = 10000;
-  o->replace_every = 50;
-  o->guess = FEM_GUESS_EXTRAP;
-  o->stop_rule = FEM_STOP_RHS;
-  o->max_refine = 4;
-  o->inner_rtol = 1e-5;
-  o->precond = FEM_PRECOND_JACOBI;
-  o->cheb_degree = 3;
-  o->cheb_ratio = 30.0;
+int create_out_of_memory() {
+  g_create_error = "host allocation failed";
+  return FEM_ENOMEM;
 }
 
-const char* fem_strerror(int status) {
-  switch (status) {
-    case FEM_OK: return "ok";
-    case FEM_EINVAL: return "invalid argument";
-    case FEM_ENOMEM: return "out of memory";
-    case FEM_ENOCONV: return "a step reached max_iter without converging";
-    case FEM_EBREAKDOWN: return "conjugate gradient breakdown";
-    case FEM_EDEVICE: return "HIP runtime error";
-    case FEM_EBUSY: return "busy";
-    case FEM_ECANCELED: return "cancelled";
-    default: return "unknown status";
-  }
-}
-
-const char* fem_last_error(const fem_heat* h) { return h ? h->err.c_str() : g_create_error.c_str(); }
-
-int fem_heat_create(const fem_grid* grid, const double* k_e, const double* rhoc_e, const fem_bc* bc,
-                    const fem_opts* opts, fem_heat** out) {
-  g_create_error.clear();
-  if (!out) return FEM_EINVAL;
-  *out = nullptr;
-  fem_opts o;
-  int rc = check_opts(opts, o, g_create_error);
-  if (rc == FEM_OK) rc = check_problem(grid, k_e, rhoc_e, bc, o, g_create_error);
-  if (rc != FEM_OK) return rc;
-  return femheat::make_handle(grid, k_e, rhoc_e, bc, o, false, out, &g_create_error);
-}
-
-int fem_heat_run(fem_heat* h, const double* T0, const double* T_prev, double dt, double theta, int32_t nsteps,
-                 double rtol, fem_out* out) {
-  if (!h) return FEM_EINVAL;
-  h->err.clear();
-  const int rc = check_run(h->g, h->devptrs, T0, dt, theta, rtol, nsteps, out, h->err);
-  if (rc != FEM_OK) return rc;
-  try {
-    return femheat::solver_run(h, T0, T_prev, dt, theta, nsteps, rtol, out);
-  } catch (const std::bad_alloc&) {
-    h->err = "host allocation failed";
-    return FEM_ENOMEM;
-  } catch (...) {
-    h->err = "unexpected exception";
-    return FEM_EDEVICE;
-  }
-}
-
-int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts, int32_t* status) {
-  g_create_error.clear();
-  g_batch_route = fem_route{};
-  if (n < 0 || (n > 0 && !reqs)) {
-    g_create_error = "reqs and n >= 0 are required";
-    return FEM_EINVAL;
-  }
-  if (n == 0) return FEM_OK;
+// fem_heat_run_batch of n > 0 requests.  (Up to the streams it may throw
+// bad_alloc; from there on it gives back what it holds.)
+int run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts, int32_t* status) {
   std::vector<int32_t> st((size_t)n, FEM_OK);
   fem_opts o;
   int rc = check_opts(opts, o, g_create_error);
@@ -319,6 +255,12 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
   hipStream_t caller = reinterpret_cast<hipStream_t>(o.hip_stream);
   std::vector<hipStream_t> gs((size_t)G, nullptr);
   std::vector<bool> own((size_t)G, false);
+  std::vector<fem_heat*> hs((size_t)n, nullptr);
+  std::vector<std::vector<femheat::RunRequest>> rq((size_t)G);
+  std::vector<std::vector<int32_t>> idx((size_t)G), gst((size_t)G);
+  std::vector<int> grc((size_t)G, FEM_OK);
+  std::vector<std::string> gerr((size_t)G);
+  std::vector<fem_route> groute((size_t)G);
   hipEvent_t start = nullptr;
   for (int g = 0; g < G && rc == FEM_OK; ++g) {
     if (G == 1 && caller) {
@@ -344,12 +286,6 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
         rc = FEM_EDEVICE;
       }
   }
-  std::vector<fem_heat*> hs((size_t)n, nullptr);
-  std::vector<std::vector<femheat::RunRequest>> rq((size_t)G);
-  std::vector<std::vector<int32_t>> idx((size_t)G), gst((size_t)G);
-  std::vector<int> grc((size_t)G, FEM_OK);
-  std::vector<std::string> gerr((size_t)G);
-  std::vector<fem_route> groute((size_t)G);
   try {
     for (int32_t i = 0; i < n && rc == FEM_OK; ++i) {
       const fem_request& r = reqs[i];
@@ -426,6 +362,89 @@ int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts,
   for (int32_t v : st)
     if (v != FEM_OK) return v;
   return FEM_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+void fem_heat_default_opts(fem_opts* o) {
+  if (!o) return;
+  std::memset(o, 0, sizeof(*o));
+  o->precision = FEM_FP64;
+  o->max_iter = 10000;
+  o->replace_every = 50;
+  o->guess = FEM_GUESS_EXTRAP;
+  o->stop_rule = FEM_STOP_RHS;
+  o->max_refine = 4;
+  o->inner_rtol = 1e-5;
+  o->precond = FEM_PRECOND_JACOBI;
+  o->cheb_degree = 3;
+  o->cheb_ratio = 30.0;
+}
+
+const char* fem_strerror(int status) {
+  switch (status) {
+    case FEM_OK: return "ok";
+    case FEM_EINVAL: return "invalid argument";
+    case FEM_ENOMEM: return "out of memory";
+    case FEM_ENOCONV: return "a step reached max_iter without converging";
+    case FEM_EBREAKDOWN: return "conjugate gradient breakdown";
+    case FEM_EDEVICE: return "HIP runtime error";
+    case FEM_EBUSY: return "busy";
+    case FEM_ECANCELED: return "cancelled";
+    default: return "unknown status";
+  }
+}
+
+const char* fem_last_error(const fem_heat* h) { return h ? h->err.c_str() : g_create_error.c_str(); }
+
+int fem_heat_create(const fem_grid* grid, const double* k_e, const double* rhoc_e, const fem_bc* bc,
+                    const fem_opts* opts, fem_heat** out) {
+  g_create_error.clear();
+  if (!out) return FEM_EINVAL;
+  *out = nullptr;
+  fem_opts o;
+  try {
+    int rc = check_opts(opts, o, g_create_error);
+    if (rc == FEM_OK) rc = check_problem(grid, k_e, rhoc_e, bc, o, g_create_error);
+    if (rc != FEM_OK) return rc;
+  } catch (const std::bad_alloc&) {
+    return create_out_of_memory();
+  }
+  return femheat::make_handle(grid, k_e, rhoc_e, bc, o, false, out, &g_create_error);
+}
+
+int fem_heat_run(fem_heat* h, const double* T0, const double* T_prev, double dt, double theta, int32_t nsteps,
+                 double rtol, fem_out* out) {
+  if (!h) return FEM_EINVAL;
+  h->err.clear();
+  try {
+    const int rc = check_run(h->g, h->devptrs, T0, dt, theta, rtol, nsteps, out, h->err);
+    if (rc != FEM_OK) return rc;
+    return femheat::solver_run(h, T0, T_prev, dt, theta, nsteps, rtol, out);
+  } catch (const std::bad_alloc&) {
+    h->err = "host allocation failed";
+    return FEM_ENOMEM;
+  } catch (...) {
+    h->err = "unexpected exception";
+    return FEM_EDEVICE;
+  }
+}
+
+int fem_heat_run_batch(const fem_request* reqs, int32_t n, const fem_opts* opts, int32_t* status) {
+  g_create_error.clear();
+  g_batch_route = fem_route{};
+  if (n < 0 || (n > 0 && !reqs)) {
+    g_create_error = "reqs and n >= 0 are required";
+    return FEM_EINVAL;
+  }
+  if (n == 0) return FEM_OK;
+  try {
+    return run_batch(reqs, n, opts, status);
+  } catch (const std::bad_alloc&) {
+    return create_out_of_memory();
+  }
 }
 
 int fem_heat_apply(fem_heat* h, int32_t which, double dt, double theta, const double* x, double* y) {
@@ -542,23 +561,22 @@ int fem_server_submit(fem_server* s, const fem_request* req, uint64_t* ticket) {
   }
   fem_opts o;
   fem_heat_default_opts(&o);  // host pointers: validation reads them directly
-  int rc = check_problem(&req->grid, req->k_e, req->rhoc_e, &req->bc, o, g_create_error);
-  if (rc == FEM_OK) {
-    femheat::Geom g{};
-    g.nx = req->grid.nx;
-    g.ny = req->grid.ny;
-    g.nz = req->grid.nz;
-    g.hx = req->grid.hx;
-    g.hy = req->grid.hy;
-    g.hz = req->grid.hz;
-    rc = check_run(g, false, req->T0, req->dt, req->theta, req->rtol, req->nsteps, req->out, g_create_error);
-  }
-  if (rc != FEM_OK) return rc;
   try {
+    int rc = check_problem(&req->grid, req->k_e, req->rhoc_e, &req->bc, o, g_create_error);
+    if (rc == FEM_OK) {
+      femheat::Geom g{};
+      g.nx = req->grid.nx;
+      g.ny = req->grid.ny;
+      g.nz = req->grid.nz;
+      g.hx = req->grid.hx;
+      g.hy = req->grid.hy;
+      g.hz = req->grid.hz;
+      rc = check_run(g, false, req->T0, req->dt, req->theta, req->rtol, req->nsteps, req->out, g_create_error);
+    }
+    if (rc != FEM_OK) return rc;
     return femheat::server_submit(s, *req, ticket, &g_create_error);
   } catch (const std::bad_alloc&) {
-    g_create_error = "host allocation failed";
-    return FEM_ENOMEM;
+    return create_out_of_memory();
   }
 }
 
