@@ -1483,7 +1483,7 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
     r.T[1] = s.T2;
     r.T[2] = s.X[0];
     r.launch = reinterpret_cast<unsigned long long*>(st.dev + o_words);
-    r.ctl = sh->res_words;
+    r.ctl = sh->res_words ? sh->res_words : reinterpret_cast<unsigned long long*>(s.X[1]);
     r.slots = r.ctl + kResCtl;
     r.stash = r.slots + res_slot_words(sh->res);
     r.fs = reinterpret_cast<const double*>(st.dev + o_fs) + at;

@@ -514,7 +514,7 @@ int solver_init(fem_heat* h, const fem_grid* grid, const double* k_e, const doub
   for (auto& p : h->pool) RC_TRY(dalloc(h, &p, N));
   if (h->nonzero_dirichlet) RC_TRY(dalloc(h, &h->lift64, N));
   RC_TRY(dalloc(h, &h->sink, kMaxBlockThreads));
-  if (h->res.nblk > 0) RC_TRY(dalloc(h, &h->res_words, res_words(h->res)));
+  if (h->res.nblk > 0 && res_words(h->res) > N) RC_TRY(dalloc(h, &h->res_words, res_words(h->res)));
   h->n_partials = std::max({h->shape.nblocks, h->upd_blocks64, h->upd_blocks32, h->start_blocks});
   const size_t ncomp = one_red ? 4 : 1;  // the one-reduction direction kernel publishes four sums per block
   for (RelayCtx* c : {&h->outer, &h->inner})
@@ -773,7 +773,7 @@ size_t handle_device_bytes(const fem_grid& grid, const fem_opts& opts, const fem
   g.py = grid.ny + 1;
   g.pz = grid.nz + 1;
   const ResShape cut = resident_shape(g, opts, true, cus);
-  if (cut.nblk > 0) bytes += 8 * res_words(cut);
+  if (cut.nblk > 0 && res_words(cut) > N) bytes += 8 * res_words(cut);
   if (n_sensors > 0) bytes += 8 * (3 * (size_t)n_sensors + (size_t)std::max(nsteps, 1) * n_sensors);
   return bytes;
 }

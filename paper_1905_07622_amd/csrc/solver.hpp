@@ -103,7 +103,7 @@ struct fem_heat {
   uint32_t upd_blocks64 = 0, upd_blocks32 = 0, start_blocks = 0;
 
   // resident form: the cut (nblk = 0: two kernels), the scratch of its blocks
-  // (res_words) and a single run's buffers
+  // (res_words; nullptr: in the fourth field buffer) and a single run's buffers
   femheat::ResShape res{};
   unsigned long long* res_words = nullptr;
   femheat::ResStage res_stage;
