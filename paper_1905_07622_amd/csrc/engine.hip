@@ -83,6 +83,7 @@ struct Sim {
   Scalars so{}, si{};  // latest settled outer and inner state
   bool resident = false;             // advances in resident launches
   uint64_t turn = 0;                 // the resident pass that it last took part in
+  bool prepared = false;             // for a resident pass, and has not taken part in one since
   uint64_t res_count[2] = {0, 0};    // its iterations and replacements so far (timing samples)
 };
 
@@ -1496,6 +1497,7 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
     r.inner_rtol = opts_.inner_rtol;
     r.spin_meet = meet_limit >= 0 ? (uint32_t)meet_limit : kResMeet;
     r.queued = first[k] ? 0 : 1;
+    r.prepared = s.prepared ? 1 : 0;
     r.hold = (uint64_t)(std::max(hold_ms, 0.0) * wall_khz_);
     r.spin = kResSpin;
     r.nsteps = steps[k];
@@ -1535,7 +1537,8 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
   ++passes_;
   for (size_t k = 0; k < n; ++k) {
     Sim& s = *act[k];
-    if (outs[k].state == RES_LATE) continue;
+    s.prepared = outs[k].state == RES_LATE;
+    if (s.prepared) continue;
     s.turn = passes_;
     if (outs[k].state == RES_LOST)
       return fail(h, FEM_EDEVICE, "a block of a resident launch stopped answering the others");

@@ -94,6 +94,7 @@ struct ResSim {
   // (last: ahead of the vectors these moved the kernels' scalar loads, 1.5% on a 201 x 201 x 26 mixed run)
   int32_t queued;             // not the first simulation of its launch (which always runs)
   uint64_t hold;              // device clock ticks that the launch lasts at most
+  int32_t prepared;           // its vectors and slots are as resident_reset_kernel left them
 };
 
 // 8-byte words of a simulation's own scratch: the control words (in a cache
