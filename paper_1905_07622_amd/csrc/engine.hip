@@ -23,17 +23,21 @@
 // the device if the solve has ended, so the GPU works through the host's
 // round trip.
 //
-// The engine advances every simulation it holds in lockstep, one step per
-// epoch, with batched launches (batch.hpp): one launch of each kernel serves
-// all simulations, each block working for one of them.  A single run is the
-// batch of one.  Between epochs, finished simulations leave the batch.
+// The engine advances every simulation in the two-kernel form in lockstep, one
+// step per epoch, with batched launches (batch.hpp): one launch of each kernel
+// serves all simulations, each block working for one of them.  A single run is
+// the batch of one.  Simulations in the resident form (resident.hpp), whose
+// grids fit on the chip, take several steps per launch, each at its own pace.
+// Between epochs, finished simulations leave the batch.
 #include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <memory>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include <hip/hip_ext.h>
@@ -1357,15 +1361,22 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
   };
   std::vector<Launch> launches;
   const ResForm form = mixed_ ? RES_MIXED : cheb_ ? RES_CHEB : RES_F64;
-  std::stable_sort(act.begin(), act.end(), [](const Sim* x, const Sim* y) {
-    const fem_heat *p = x->rq.h, *q = y->rq.h;
-    if (p->kind != q->kind) return p->kind < q->kind;
-    if (p->res.c != q->res.c) return p->res.c < q->res.c;
-    return x->turn < y->turn;  // those that the last launch had no time for go first
+  // Those that the last pass had no time for go first, in their launch and with
+  // it: the time is the pass's, and a later launch may find none of it left.
+  // (With the launches always in one order, the later ones took one step of one
+  // simulation per pass while the first was busy.)
+  auto key = [](const Sim* s) { return std::make_pair(s->rq.h->kind, s->rq.h->res.c); };
+  std::map<std::pair<int, int>, uint64_t> waits;  // oldest turn of a launch's simulations
+  for (const Sim* s : act) {
+    const auto it = waits.emplace(key(s), s->turn).first;
+    it->second = std::min(it->second, s->turn);
+  }
+  std::stable_sort(act.begin(), act.end(), [&](const Sim* x, const Sim* y) {
+    const auto p = key(x), q = key(y);
+    return p == q ? x->turn < y->turn : std::make_pair(waits[p], p) < std::make_pair(waits[q], q);
   });
   const size_t n = act.size();
   std::vector<int> steps(n);
-  std::vector<char> first(n, 0);  // of its launch
   size_t nsteps = 0, nblocks = 0;
   uint32_t max_nodes = 0;
   for (size_t k = 0; k < n; ++k) {
@@ -1381,7 +1392,6 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
       l.planes = sh->res.c;
       l.off = (uint32_t)nblocks;
       launches.push_back(l);
-      first[k] = 1;
     }
     Launch& l = launches.back();
     l.nthreads = std::max(l.nthreads, sh->res.nthreads);
@@ -1496,7 +1506,7 @@ int Engine::resident_pass(const ResBounds& bounds, int* advanced) {
     r.rtol2 = s.rq.rtol * s.rq.rtol;
     r.inner_rtol = opts_.inner_rtol;
     r.spin_meet = meet_limit >= 0 ? (uint32_t)meet_limit : kResMeet;
-    r.queued = first[k] ? 0 : 1;
+    r.queued = k == 0 ? 0 : 1;
     r.prepared = s.prepared ? 1 : 0;
     r.hold = (uint64_t)(std::max(hold_ms, 0.0) * wall_khz_);
     r.spin = kResSpin;

@@ -92,7 +92,7 @@ struct ResSim {
   uint32_t spin_meet, spin;   // polls before a wait gives up
   int32_t nsens, nsteps, max_iter, stop_rule, R, guess_prev, max_refine, timing, chain;
   // (last: ahead of the vectors these moved the kernels' scalar loads, 1.5% on a 201 x 201 x 26 mixed run)
-  int32_t queued;             // not the first simulation of its launch (which always runs)
+  int32_t queued;             // not the first simulation of its pass (which always runs)
   uint64_t hold;              // device clock ticks that the launch lasts at most
   int32_t prepared;           // its vectors and slots are as resident_reset_kernel left them
 };

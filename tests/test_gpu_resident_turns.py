@@ -5,6 +5,7 @@ import pytest
 
 from paper_1905_07622_amd import femheat as fh
 from paper_1905_07622_amd import workloads as wl
+from _util import say
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,20 @@ def test_turns_change_no_bits(gpu, monkeypatch, opts):
     for a, b in zip(turns, whole):
         for key in ("T_final", "iters", "relres"):
             assert np.array_equal(a[key], b[key]), key
+
+
+def test_launches_of_a_pass_take_turns(gpu):
+    """Requests of one size class that run in two kernels (boxes, and cubic
+    elements), steps as long as a launch may last: the ones do not wait until
+    the others are done.  In turns, 8 short requests take one step each in every
+    second epoch; one step of one of them in each epoch would be 64 epochs."""
+    short = [wl.random_problem(20, 20, 20, seed=s, nsteps=8, rtol=1e-30) for s in range(8)]
+    long = [p.replace(hz=1.5 * p.hz, nsteps=60) for p in short[:4]]
+    with fh.Server(max_iter=600) as s:
+        running = [s.submit(p) for p in long]
+        for t in [s.submit(p) for p in short]:
+            assert s.wait(t)[0] == fh.FEM_ENOCONV
+        epochs = s.info()["epochs"]
+        assert any(s.poll(t)["state"] == fh.FEM_REQ_RUNNING for t in running)
+    say(f"  {epochs} epochs")
+    assert epochs <= 32
