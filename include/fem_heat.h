@@ -78,8 +78,8 @@ extern "C" {
                                    Applied matrix-free as m steps of the Chebyshev iteration from 0
                                    (m - 1 gathers per application).  Not in the paper, whose GPU
                                    method uses Jacobi only.  The stop rule's norm (P^-1 above) is
-                                   M^-1.  FP64 two-kernel form only (FEM_EINVAL with the mixed form
-                                   or FEM_ONE_REDUCTION) */
+                                   M^-1.  FP64 only (FEM_EINVAL with the mixed form or
+                                   FEM_ONE_REDUCTION) */
 
 #define FEM_DEVICE_PTRS 0x1u /* array arguments are device pointers               */
 #define FEM_TIMING 0x2u      /* time iteration kernels with HIP events (every 64th iteration and every
@@ -193,7 +193,8 @@ typedef struct {
   double cheb_ratio;      /* Chebyshev: hi / lo of the interval, > 1 (default 30)            */
   int32_t element;        /* FEM_ELEM_* (default FEM_ELEM_HEX8)                              */
   const char *tune_cache; /* path of the autotuner's tile cache (JSON), or NULL.  When set and no
-                             tile override is given, a handle takes the gather tile recorded
+                             tile override is given, a handle takes for its two-kernel launches (a
+                             run in the resident form has no tile) the gather tile recorded
                              there for its node grid, precision, element class and launch kind
                              (alone or batch member) on this GPU architecture and HIP runtime;
                              fem_heat_tune records into it (see fem_heat_tune on results). */
@@ -201,7 +202,9 @@ typedef struct {
                              dealt round-robin, each on its own stream and host thread, so that one
                              batch's last iterations (its slowest members) overlap the others'
                              work; results do not change.  0 = automatic (one batch per 16
-                             simulations and per 2^21 nodes in all, at most 3, at least 1);
+                             simulations and per 2^21 nodes, at most 3, at least 1; simulations
+                             that run in the resident form do not count for it: they share the
+                             device by themselves);
                              with a caller's stream the batches start after its earlier work.
                              Handles and servers ignore it (server lanes already overlap) */
 } fem_opts;
@@ -277,16 +280,22 @@ int fem_heat_create(const fem_grid *grid, const double *k_e, const double *rhoc_
  * FEM_ENOCONV (some step hit max_iter: all outputs written, iters = max_iter
  * marks the step) or FEM_EBREAKDOWN (outputs up to the last good step).
  *
- * A simulation whose grid fits on the chip (up to about 1.1 million nodes with
- * the Jacobi preconditioner, 0.65 million with Chebyshev of degree 2 to 5; no
- * tile override, neither FEM_ONE_REDUCTION nor FEM_ONE_KERNEL) runs in the resident form: one kernel takes many steps, its
- * blocks each keep a brick of the grid in LDS and registers and exchange sums
- * and brick surfaces.  The same holds for batch members and served requests.
+ * A simulation whose grid fits on the chip (no tile override, neither
+ * FEM_ONE_REDUCTION nor FEM_ONE_KERNEL) runs in the resident form: one kernel
+ * takes many steps, its blocks each keep a brick of the grid in LDS and
+ * registers and exchange sums and brick surfaces.  A grid fits if it can be cut
+ * into at most 256 bricks (one per compute unit) of at most 512 columns and 9
+ * planes with 159 KB of LDS each: cubes of up to 102^3 nodes with the Jacobi
+ * preconditioner, 90^3 with Chebyshev of degree 2 to 5, at most 131072
+ * columns of nodes whatever the height, and not every shape below that
+ * (151 x 151 x 46 nodes does not).  The same holds for batch members and served
+ * requests.  fem_heat_route tells which form ran.
  * The kernel needs all blocks of a simulation at once: resident launches of one
- * process take turns where they would not all fit, and a launch whose blocks do
- * not all get compute units within 20 ms (another process, or a stream with
- * a compute-unit mask, holds them) does nothing, and the run goes on with the
- * two-kernel form (whose fields agree to rounding). */
+ * process take turns where they would not all fit, each for about 100 ms at
+ * most (or one step, if that is longer), and a simulation whose blocks do not
+ * all get compute units within 20 ms in which no other simulation of its launch
+ * runs (another process, or a stream with a compute-unit mask, holds them) goes
+ * on in the two-kernel form, whose fields agree to rounding. */
 int fem_heat_run(fem_heat *h, const double *T0, const double *T_prev, double dt, double theta,
                  int32_t nsteps, double rtol, fem_out *out);
 
@@ -329,39 +338,48 @@ typedef struct {
 /* Run n independent simulations together on one GPU: the repeated forward
  * solves of a coefficient study (Sec. 5.4), each with its own grid,
  * coefficients, boundary conditions, dt, theta, rtol and step count.  Every
- * kernel launch serves all of them (a simulation's blocks work only on its
- * own data, with its own reductions), they advance one time step per epoch
- * in lockstep, and each leaves the batch after its last step.  A
- * simulation's results do not depend on the others in the batch: they are
- * bit-identical to those of a batch holding it alone.  Large batches run as
- * a few such batches at once (fem_opts.batch_groups).  opts (may be NULL)
- * apply to all: precision, iteration controls, flags (FEM_DEVICE_PTRS covers
- * every array of every request), stream, device and tile overrides; without
- * a tile_z override every simulation marches z-chunks of at most 32 planes.
- * Validates every request first and runs none if one is invalid
- * (FEM_EINVAL, status[i] names it).  Otherwise status[i] (n entries, may be
- * NULL) receives each simulation's outcome as fem_heat_run would return it,
- * and the call returns FEM_OK when all are FEM_OK, else the first other
- * status in request order; FEM_ENOMEM / FEM_EDEVICE abort the whole batch. */
+ * kernel launch serves all of them (a simulation's blocks work only on its own
+ * data, with its own reductions), and each leaves the batch after its last
+ * step.  Members in the two-kernel form advance one time step per epoch in
+ * lockstep; members in the resident form (see fem_heat_run) iterate each at
+ * its own pace, several steps per launch.  A simulation's results do not
+ * depend on the others in the batch: they are bit-identical to those of a
+ * batch holding it alone (unless, in one of the two, its blocks did not meet:
+ * see fem_heat_run).  Large batches of members in the two-kernel form run as a
+ * few such batches at once (fem_opts.batch_groups).  opts (may be NULL) apply
+ * to all: precision, iteration controls, flags (FEM_DEVICE_PTRS covers every
+ * array of every request), stream, device and tile overrides; without a tile_z
+ * override every simulation marches z-chunks of at most 32 planes. Validates
+ * every request first and runs none if one is invalid (FEM_EINVAL, status[i]
+ * names it).  Otherwise status[i] (n entries, may be NULL) receives each
+ * simulation's outcome as fem_heat_run would return it, and the call returns
+ * FEM_OK when all are FEM_OK, else the first other status in request order;
+ * FEM_ENOMEM / FEM_EDEVICE abort the whole batch. */
 int fem_heat_run_batch(const fem_request *reqs, int32_t n, const fem_opts *opts, int32_t *status);
 
 /* ---- serving: continuous batching of forward simulations ------------------
  *
- * A server groups requests into size classes (the binary order of magnitude
- * of their node count); each class has a lane, a worker thread with its own
- * HIP stream, that advances every admitted simulation of the class one time
- * step per epoch with the batched launches of fem_heat_run_batch, so the
- * classes run concurrently and a small request never waits for the epochs of
- * a large one.  Submitted requests wait in one FIFO queue; at each of its
- * epoch boundaries a lane retires its finished simulations (outputs written,
- * device memory released to the server's stream-ordered pool, completion
- * stamped) and admits queued requests of its class in arrival order while
- * their device footprint fits the free part of the HBM budget and a slot is
- * free (a request that does not fit blocks every later one, so large
- * requests cannot starve).  An admitted simulation
- * keeps its whole PCG state resident until it finishes, and joins the
- * launches at the next epoch while the others continue: its results are
- * bit-identical to those of a batch holding it alone.  The use case is the
+ * A server groups requests into size classes (the binary order of magnitude of
+ * their node count); each class has a lane, a worker thread with its own HIP
+ * stream, that advances every admitted simulation of the class with the
+ * batched launches of fem_heat_run_batch: per epoch one time step in the
+ * two-kernel form, where the classes run concurrently, or up to four steps in
+ * one resident launch (see fem_heat_run).  Resident launches of the classes
+ * take turns where they do not all fit on the device, so a small request may
+ * wait for a launch of larger ones, which gives the device back at the end of
+ * the step it is in once it has lasted 2 ms; simulations whose turn has not
+ * come by then go first in the lane's next launch.  Submitted requests wait in
+ * one FIFO queue; at each of its epoch boundaries a lane retires its finished
+ * simulations (outputs written, device memory released to the server's
+ * stream-ordered pool, completion stamped) and admits queued requests of its
+ * class in arrival order while their device footprint fits the free part of
+ * the HBM budget and a slot is free (a request that does not fit blocks every
+ * later one, so large requests cannot starve).  An admitted simulation keeps
+ * its whole PCG state resident until it finishes, and joins the launches at
+ * the next epoch while the others continue: its results are bit-identical to
+ * those of a batch holding it alone (unless, in one of the two, its blocks did
+ * not meet: see fem_heat_run).  steps_done, cancellation and admission move
+ * from epoch to epoch, that is by up to four steps.  The use case is the
  * paper's coefficient study of thousands of forward solves (Sec. 5.4). */
 
 #define FEM_REQ_QUEUED 0
@@ -422,8 +440,8 @@ int fem_server_info_get(fem_server *s, fem_server_info *info);
 /* Cancel everything outstanding, stop the worker and release the server. */
 void fem_server_destroy(fem_server *s);
 
-/* Autotuner (the project's own; the paper tunes nothing).  Times the
- * hot gather of the PCG iteration -- search-direction update fused with the
+/* Autotuner (the project's own; the paper tunes nothing).  Times the hot
+ * gather of the PCG iteration -- search-direction update fused with the
  * operator apply q = A d and the previous iteration's x += alpha d, in the
  * handle's precision (FP32 for the mixed form) -- on this handle's grid and
  * coefficients for a set of candidate tiles (x pieces of the node row, block
@@ -431,20 +449,21 @@ void fem_server_destroy(fem_server *s);
  * device events over repeated launches, and installs the fastest on the
  * handle.  With FEM_TUNE_BATCH the candidates and the timing are those of a
  * batch member: chunks of 8 to 32 planes or the node column cut into 1 to 6
- * equal chunks, each scored by its time per simulation in a launch with
- * enough copies of the simulation to fill the device plus a sixteenth of a
- * launch holding the simulation alone (a lockstep batch ends each step with
- * launches serving only its slowest members, where the tile's latency
- * counts); the tile is recorded, not installed.  When the
- * handle's options name a tune_cache, the result is recorded there under
- * the key of this grid, precision, element class and launch kind, and later
- * handles (fem_heat_create, fem_heat_run_batch, servers) with the same
- * options take it.  The operator's value at every node does not depend on
- * the tile (its sums are formed in a fixed order), but a run's dot products
- * are summed per block, so another tile changes results at rounding level;
- * the same tile repeats a run bit for bit.  The handle's vectors are overwritten:
- * tune before a run, not between the two halves of a resumed run.  out may
- * be NULL. */
+ * equal chunks, each scored by its time per simulation in a launch with enough
+ * copies of the simulation to fill the device plus a sixteenth of a launch
+ * holding the simulation alone (a lockstep batch ends each step with launches
+ * serving only its slowest members, where the tile's latency counts); the tile
+ * is recorded, not installed.  A run in the resident form (see fem_heat_run)
+ * has no tile: there the tuned one serves fem_heat_apply and a run whose
+ * blocks did not meet.  When the handle's options name a tune_cache, the
+ * result is recorded there under the key of this grid, precision, element
+ * class and launch kind, and later handles (fem_heat_create,
+ * fem_heat_run_batch, servers) with the same options take it.  The operator's
+ * value at every node does not depend on the tile (its sums are formed in a
+ * fixed order), but a run's dot products are summed per block, so another tile
+ * changes results at rounding level; the same tile repeats a run bit for bit.
+ * The handle's vectors are overwritten: tune before a run, not between the two
+ * halves of a resumed run.  out may be NULL. */
 #define FEM_TUNE_BATCH 0x1
 typedef struct {
   int32_t tile_x, tile_y, tile_z; /* installed tile                                         */

@@ -16,8 +16,10 @@ void engine_delete(Engine* e);
 // Prepares a simulation on its handle (whose stream must be the engine's);
 // it joins the batch at the next epoch.
 int engine_add(Engine* e, const RunRequest& r, Sim** out);
-// One epoch: every member with steps left advances one step; *active is the
-// number that did (0: nothing to do).  A failing HIP call fails the epoch.
+// One epoch: every member with steps left advances by one step (in the
+// resident form by up to four, or by none where the launch's time is over
+// before its turn); *active is how many had steps left (0: nothing to do).  A
+// failing HIP call fails the epoch.
 int engine_step(Engine* e, int* active);
 bool engine_sim_finished(const Sim* s);
 int engine_sim_status(const Sim* s);

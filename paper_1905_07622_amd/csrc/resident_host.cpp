@@ -35,15 +35,16 @@ std::array<GateState, kMaxDevices>& gates() {
 }  // namespace
 
 // Estimated microseconds of an iteration of a cut, a linear fit to 250 cuts
-// (taken before the iterations and the waits were shortened by 4 to 15%)
 // measured on grids of 17^3, 49^3, 58 x 84 x 40 (stretched), 91 x 91 x 31
 // (tetrahedra) and 101^3 nodes (MI355X, FP64): the two sums take 3.8 us and
 // 6.7 ns per block, a layer of the march 0.38 us with one wave per SIMD and
 // 0.55 us with two, a halo node that a brick shares across an x-face 4.5 ns
 // (its values lie a row apart) and any other 0.7 ns.  So full rows and low
-// bricks win where they fit: 49^3 as 49 x 5 x 3 takes 6.9 us, as 25 x 10 x 5
+// bricks win where they fit: 49^3 as 49 x 5 x 3 took 6.9 us, as 25 x 10 x 5
 // 7.8 us, as 49 x 10 x 9 10.3 us; 17^3 as 17 x 6 x 3 6.7 us, in two bricks
-// 11.6 us.  A simulation alone takes the cut with the shortest iteration; a
+// 11.6 us.  (These figures are the fit's, which ranks the cuts.  Iterations and
+// waits have become 4 to 15% shorter since, on every cut: the chosen ones take
+// 5.9 us on 49^3 and 5.8 us on 17^3 now.)  A simulation alone takes the cut with the shortest iteration; a
 // batch member the one with the least iteration time per compute unit, as
 // other members fill the rest.  A step of the Chebyshev preconditioner's chain
 // is another march and an exchange without a sum (1.9 us): at degree 3 the

@@ -1,16 +1,19 @@
 // Serving loop: continuous batching of forward simulations on one GPU.
 //
 // Requests are grouped into size classes (the binary order of magnitude of
-// their node count).  Each class has a lane: a worker thread with its own
-// HIP stream and engine, so the classes' kernels run concurrently and a
-// small request never waits for the epochs of a large one.  Each turn of a
-// lane's loop is one epoch boundary: finished simulations retire (outputs,
-// memory, completion stamp), cancelled ones leave, queued requests of the
-// lane's class are admitted while their device footprint fits the free
-// budget and a slot is free, and then every simulation of the lane advances
-// one time step with the batched launches.  Admission follows arrival order
-// across all classes: a request that does not fit blocks every later one,
-// so large requests cannot starve.
+// their node count).  Each class has a lane: a worker thread with its own HIP
+// stream and engine.  Kernels of the two-kernel form of different classes run
+// concurrently; resident launches (resident.hpp) take turns where they do not
+// all fit on the device, each for about 2 ms (kResServe), and that long a
+// small request may wait for a large one.  Each turn of a lane's loop is one
+// epoch boundary: finished simulations retire (outputs, memory, completion
+// stamp), cancelled ones leave, queued requests of the lane's class are
+// admitted while their device footprint fits the free budget and a slot is
+// free, and then every simulation of the lane advances with the batched
+// launches: one time step in the two-kernel form, up to four in a resident
+// launch (none where the launch's time is over before its turn).  Admission
+// follows arrival order across all classes: a request that does not fit blocks
+// every later one, so large requests cannot starve.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
